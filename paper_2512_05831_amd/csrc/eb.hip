@@ -40,10 +40,14 @@
 //     cache (best for skewed ids).  Under the no-reuse hint block ids are
 //     remapped so each XCD gets a contiguous run of bags (measured faster for
 //     uniform ids).
-// Rows that no chunk width fits (sizes not a multiple of 4 bytes, tables or
-// outputs aligned to less than 4 bytes, narrow chunks beyond 64 per row, rows
-// wider than 8 KB) take a plain one-wave-per-bag kernel: all lanes read a
-// row's columns with element-sized loads, 8 rows in flight.
+// The wave kernel (eb_gather_wave.h) takes a wave, or up to 16, per bag: small
+// batches, long bags of cached rows, and every row of 16 bytes to 8 KB that no
+// aligned chunk width fits (use_wave in eb_gather.h says where each is faster),
+// for tables of less than 4 GB of gatherable rows.
+// What is left (rows under 16 bytes whose size is not a multiple of 4, rows
+// wider than 8 KB, and, in larger tables or at odd addresses, rows no chunk
+// width fits) takes a plain one-wave-per-bag kernel: all lanes read a row's
+// columns with element-sized loads, 8 rows in flight.
 
 #include <hip/hip_runtime.h>
 
@@ -180,6 +184,7 @@ int forward_impl(const char *who, const eb_tables *h, int32_t T, const int64_t *
     if (out_cols && columns_overlap(out_cols, T, D)) return fail(EB_ERR_INVALID, "%s: two tables share output columns", who);
     if (hits && (ldh < T || B > kMax / ldh)) return fail(EB_ERR_INVALID, "%s: bad ldh (must be >= T with B*ldh in int64)", who);
 
+    int64_t most_rows = 0;
     for (int32_t t = 0; t < T; ++t) {
         if (rows[t] < 0) return fail(EB_ERR_INVALID, "%s: negative rows[t]", who);
         const int64_t n = local_rows(rows[t], shard_lo, shard_hi);
@@ -188,14 +193,15 @@ int forward_impl(const char *who, const eb_tables *h, int32_t T, const int64_t *
                         who, (int)t);
         if ((uint64_t)n > kMaxLocalRows)
             return fail(EB_ERR_UNSUPPORTED, "%s: more than 4294967294 gatherable rows in a table", who);
+        most_rows = std::max(most_rows, n);
     }
 
     // Vector stores need every (bag, table) output row start aligned to them.
     int out_align = std::min(pow2_align((uintptr_t)out), pow2_align((uintptr_t)ldo * 4));
     for (int32_t t = 0; t < T; ++t)
         out_align = std::min(out_align, pow2_align((uintptr_t)out_col(out_cols, t, D) * 4));
-    const GatherPlan plan = plan_gather(D, dtype, h->align, out_align, index_type == EB_IDX_I32, weights != nullptr,
-                                        T, B, nnz, mode);
+    const GatherBuffers buffers{h->align, out_align, pow2_align((uintptr_t)offsets), most_rows};
+    const GatherPlan plan = plan_gather(D, dtype, buffers, index_type == EB_IDX_I32, weights != nullptr, T, B, nnz, mode);
     if (!plan.fn) return fail(EB_ERR_UNSUPPORTED, "%s: no kernel for this row shape", who);
 
     GatherArgs a;
@@ -209,8 +215,10 @@ int forward_impl(const char *who, const eb_tables *h, int32_t T, const int64_t *
     a.ldo = ldo;
     a.ldh = ldh;
     a.D = D;
-    a.row_bytes = plan.team ? D * elem_bytes(dtype) : 0;
-    a.chunks = plan.team ? D * elem_bytes(dtype) / plan.chunk_bytes : 0;
+    if (plan.chunk_bytes > 0) {
+        a.row_bytes = D * elem_bytes(dtype);
+        a.chunks = (a.row_bytes + plan.chunk_bytes - 1) / plan.chunk_bytes;
+    }
     a.mean = pool == EB_MEAN;
     a.xcd_runs = plan.xcd_runs ? 1 : 0;
 
@@ -225,7 +233,7 @@ int forward_impl(const char *who, const eb_tables *h, int32_t T, const int64_t *
         }
         a.offsets = (const char *)offsets + (size_t)t0 * B * ies;
         a.hits = hits ? hits + t0 : nullptr;
-        const hipError_t err = launch_gather(plan, a, nt, (hipStream_t)stream);
+        const hipError_t err = launch_gather(plan, a, nt, dtype, (hipStream_t)stream);
         if (err != hipSuccess) return fail(EB_ERR_HIP, "%s: kernel launch failed: %s", who, hipGetErrorString(err));
     }
     return EB_OK;

@@ -22,6 +22,7 @@ constexpr int kBlock = kWave * kWavesPerBlock;
 constexpr int kXcds = 8;
 constexpr int kMaxTablesPerLaunch = 64;
 constexpr int kStagePerWave = 256;                // LDS index window, entries per wave
+constexpr int kMaxSplit = 16;                     // waves per bag of the wave kernel
 constexpr uint32_t kInvalidRow = 0xFFFFFFFFu;     // never a staged row: local rows stay below it
 constexpr uint64_t kMaxLocalRows = 0xFFFFFFFEull; // local rows must fit below the marker
 
@@ -44,11 +45,12 @@ struct GatherArgs {
     int64_t ldh;
     int32_t D;
     int32_t row_bytes;      // D * element bytes
-    int32_t chunks;         // row_bytes / 16 (team kernel)
+    int32_t chunks;         // chunks per row (the wave kernel's last one may overlap its neighbour)
     int32_t blocks_per_table;
     int32_t nblocks;        // logical blocks; the grid is padded to a multiple of 8
     int32_t mean;
     int32_t xcd_runs;       // give each XCD a contiguous run of logical blocks
+    int32_t split;          // waves per bag (wave kernel)
 };
 
 // ---------------------------------------------------------------------------- device helpers
@@ -716,6 +718,10 @@ KernelFn pick_narrow_kernel(bool weighted, bool i32, int dtype, int cb, int R, b
                             bool single);
 KernelFn pick_narrow_weighted_kernel(bool i32, int dtype, int cb, int R, bool stream, bool few, bool single);
 
+// Wave kernels (eb_gather_wave.h), weighted or not.
+KernelFn pick_wave_kernel(bool weighted, bool i32, int dtype, int R, int C, bool stream);
+KernelFn pick_wave_weighted_kernel(bool i32, int dtype, int R, int C, bool stream);
+
 inline int elem_bytes(int dtype) { return dtype == EB_F32 ? 4 : 2; }
 
 // ---------------------------------------------------------------------------- launch shape (host)
@@ -765,7 +771,16 @@ struct GatherPlan {
     bool team;           // team kernel (else plain)
     int bags_per_block;
     bool xcd_runs;       // each XCD takes a contiguous run of workgroups
-    int chunk_bytes;     // team kernel: bytes of a row one lane loads at a time
+    int chunk_bytes;     // bytes of a row one lane loads at a time (0: plain kernel)
+    int split;           // wave kernel: waves per bag (0: team or plain kernel)
+};
+
+// What a call's buffers allow (host side of plan_gather).
+struct GatherBuffers {
+    int table_align;      // largest power of two up to 16 dividing every table pointer
+    int out_align;        // ... every output row start in bytes
+    int offsets_align;    // ... the offsets pointer
+    int64_t local_rows;   // most gatherable rows of a table
 };
 
 // Chunk size of the team kernel for rows of rb bytes, or 0 for the plain
@@ -786,12 +801,85 @@ inline int chunk_bytes(int64_t rb, int dtype, int table_align, int out_align)
     return 0;
 }
 
-inline GatherPlan plan_gather(int32_t D, int32_t dtype, int table_align, int out_align, bool i32, bool weighted,
+// Whether the wave kernel (eb_gather_wave.h) can read these rows: 16 bytes to
+// 8 KB each, element-aligned tables, float-aligned output rows, table offsets
+// that fit its 32-bit product, and offsets that scalar loads can read.
+inline bool wave_fits(int64_t rb, int dtype, const GatherBuffers &buf)
+{
+    return rb >= 16 && rb <= 8192 && buf.table_align >= elem_bytes(dtype) && buf.out_align >= 4 &&
+           buf.offsets_align >= 4 && buf.local_rows <= (int64_t)(0xFFFFFFFFu / (uint64_t)rb);
+}
+
+// Whether a call takes the wave kernel rather than a team or plain kernel.
+// A wave per bag costs a large batch of short bags more waves than a team per
+// bag does, and gains from cheaper loads as bags grow.  P = 64 / R rows are
+// read at a time; all times in us, team or plain kernel against wave kernel,
+// kernel traces:
+//   * rows no aligned chunk fits: always (16 tables x 4096 bags of 20 ids of
+//     189 fp16: 306 against 90, of 1 id: 42.6 against 30.3).
+//   * small batches, where the chain of dependent loads is the time: always up
+//     to 2048 bags (8 x 256 bags of 16 ids of 64 fp32: 4.8 against 4.0; one bag
+//     of 1 id in 32: 4.2 against 3.8); up to 8192 when a bag fills two passes
+//     or rows have 256 bytes or more (64 x 128 bags of 64 fp32, 1 id: 6.0
+//     against 4.6, 16 ids: 10.2 against 8.6; of 32 fp32, 4 ids: 4.4 against
+//     4.9, 16 ids: 6.8 against 6.4), except streamed 512-byte rows in shorter
+//     bags (1 id: 5.1 against 5.6).
+//   * cached or ragged rows: bags of four passes on average, at most a window
+//     (16 x 4096 bags, skewed ids: 128-B rows, 16 ids: 20.7 against 23.5, 32
+//     ids: 35.3 against 30.1, 64 ids: 67.7 against 45.6; 256-B rows, 8 / 16 /
+//     32 ids: 21.5 / 32.2 / 59.0 against 25.0 / 31.2 / 47.4; 512-B rows, 4 / 8
+//     / 16 ids: 24.6 / 36.4 / 62.4 against 26.9 / 36.0 / 52.1; 1-KB rows, 2 / 4
+//     / 8 ids: 30.6 / 42.2 / 68.5 against 34.2 / 41.7 / 60.4; 64-B rows, 32 /
+//     64 ids: 24.3 / 47.4 against 27.9 / 42.2).  Streamed rows are bound by
+//     HBM: those of 16-byte chunks keep the teams, as do rows under 128 B (24-B
+//     rows, 60 uniform ids: 65.4 against 72.1).
+//   * 16-byte rows of more than 2 KB stay with the teams (8-KB rows, 2048 bags
+//     of 100 ids: 253 against 283).
+inline bool use_wave(int64_t rb, int cb, const Shape &whole, bool hint, int64_t bags, int64_t nnz)
+{
+    if (cb == 0) return true;
+    if (cb == 16 && whole.C > 2) return false;
+    if (bags <= kFewBagsMax) return true;
+    const int R = whole.R, P = kWave / R;
+    const bool stream = hint && rb >= 128;
+    if (bags <= kWaveSlots && (nnz >= 2 * P * bags || (rb >= 256 && !(stream && R == 32)))) return true;
+    if (hint && (cb == 16 || rb < 128)) return false;
+    return nnz >= (int64_t)(4 * P < kWave ? 4 * P : kWave) * bags;
+}
+
+// Waves per bag of the wave kernel, a power of two: more than one when a bag
+// per wave would leave at least half the GPU's wave slots empty, as long as a
+// wave keeps 48 ids and the partial sums fit 32 KB of LDS (64-column fp32
+// rows, 1 / 2 / 4 / 8 / 16 waves: 32 bags of 100 ids 5.0 / 4.7 / 4.4 / 4.5 /
+// 4.6 us, of 2000 ids 59.0 / 31.4 / 18.2 / 11.2 / 10.3; 512 bags of 400 ids
+// 15.6 / 11.1 / 10.5 / 10.4 / 10.3; 2048 bags of 400 ids 27.7 / 29.2 / 28.3 /
+// 28.2 / 30.5; the team kernel: 5.6, 49.4, 14.2, 28.4).
+inline int split_waves(int64_t bags, int64_t nnz, int64_t rb, int dtype)
+{
+    const int64_t wave_lds = (rb + 15) / 16 * (16 / elem_bytes(dtype)) * (int64_t)sizeof(float);
+    int split = 1;
+    while (split < kMaxSplit && 2 * bags * split <= kWaveSlots / 2 && nnz >= 48 * split * bags &&
+           2 * split * wave_lds <= 32768)
+        split *= 2;
+    return split;
+}
+
+inline GatherPlan plan_gather(int32_t D, int32_t dtype, const GatherBuffers &buf, bool i32, bool weighted,
                               int64_t T, int64_t B, int64_t nnz, int32_t mode)
 {
-    GatherPlan plan{nullptr, false, kWavesPerBlock, false, 0};
+    GatherPlan plan{nullptr, false, kWavesPerBlock, false, 0, 0};
     const int64_t rb = (int64_t)D * elem_bytes(dtype);
-    const int cb = chunk_bytes(rb, dtype, table_align, out_align);
+    const int cb = chunk_bytes(rb, dtype, buf.table_align, buf.out_align);
+    const bool hint = (mode & EB_HINT_STREAM_ROWS) != 0;
+    const bool fits = wave_fits(rb, dtype, buf);
+    const Shape whole = team_shape(fits ? (int)((rb + 15) / 16 * 16) : 16, 16, true, false); // a wave per bag
+    if (fits && use_wave(rb, cb, whole, hint, T * B, nnz)) {
+        plan.fn = pick_wave_kernel(weighted, i32, dtype, whole.R, whole.C, hint && rb >= 128);
+        plan.chunk_bytes = 16;
+        plan.split = split_waves(T * B, nnz, rb, dtype);
+        plan.bags_per_block = plan.split > 1 ? 1 : kWavesPerBlock;
+        return plan;
+    }
     plan.team = cb > 0;
     plan.chunk_bytes = cb;
     if (!plan.team) {
@@ -800,7 +888,6 @@ inline GatherPlan plan_gather(int32_t D, int32_t dtype, int table_align, int out
         return plan;
     }
     // Non-temporal loads lose for rows narrower than 128 bytes.
-    const bool hint = (mode & EB_HINT_STREAM_ROWS) != 0;
     const bool stream = hint && rb >= 128;
     const Shape normal = team_shape((int)rb, cb, false, false);
     const int64_t bags = T * B;
@@ -834,10 +921,16 @@ inline GatherPlan plan_gather(int32_t D, int32_t dtype, int table_align, int out
     return plan;
 }
 
+// LDS for the partial sums of a split bag.
+inline size_t split_lds_bytes(int split, int chunks, int dtype)
+{
+    return split > 1 ? (size_t)split * chunks * (16 / elem_bytes(dtype)) * sizeof(float) : 0;
+}
+
 // Launch one piece of at most 64 tables (a.base / nlocal / col / offsets /
 // hits already set for it), in as many launches as the grid bound needs:
 // each launch covers a range of every table's bags.
-inline hipError_t launch_gather(const GatherPlan &plan, GatherArgs &a, int32_t nt, hipStream_t stream)
+inline hipError_t launch_gather(const GatherPlan &plan, GatherArgs &a, int32_t nt, int dtype, hipStream_t stream)
 {
     const int64_t kMaxBlocks = (int64_t)1 << 22;
     const int64_t blocks_all_bags = (a.B + plan.bags_per_block - 1) / plan.bags_per_block;
@@ -847,6 +940,15 @@ inline hipError_t launch_gather(const GatherPlan &plan, GatherArgs &a, int32_t n
         a.bag_begin = blk0 * plan.bags_per_block;
         a.blocks_per_table = (int32_t)bpt;
         a.nblocks = (int32_t)(bpt * nt);
+        if (plan.split > 0) {
+            a.split = plan.split;
+            void *wargs[] = {&a};
+            const hipError_t err = hipLaunchKernel((const void *)plan.fn, dim3((unsigned)bpt, (unsigned)nt),
+                                                   dim3(plan.split > 1 ? kWave * plan.split : kBlock), wargs,
+                                                   split_lds_bytes(plan.split, a.chunks, dtype), stream);
+            if (err != hipSuccess) return err;
+            continue;
+        }
         const int64_t grid = plan.xcd_runs ? (a.nblocks + kXcds - 1) / kXcds * kXcds : a.nblocks;
         void *args[] = {&a};
         const hipError_t err = hipLaunchKernel((const void *)plan.fn, dim3((unsigned)grid), dim3(kBlock), args, 0, stream);
