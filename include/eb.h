@@ -280,18 +280,22 @@ int eb_bucketize_workspace(int32_t T, int64_t B, int32_t G, size_t *bytes);
  *                owned by the caller; its contents are not kept.
  *   stream       a hipStream_t (NULL = the null stream); asynchronous.
  *
- * Paths: batches of at least 3,670,016 ids with at most 16 destinations and 1024
- * tables (and, inside a graph capture, once an eager call has run on the
- * process's device) run a one-pass kernel that reads every
+ * Paths: batches of fewer than 3,670,016 ids (5,242,880 for 17 to 32
+ * destinations) with at most 64 destinations, whose bags fit 768 workgroups of
+ * at most 255 bags of one table (and whose offsets and bounds are 4-byte,
+ * workspace 16-byte aligned), run as two kernels.  Batches of at least 3,670,016 ids with
+ * at most 16 destinations and 1024 tables (and, inside a graph capture, once
+ * an eager call has run on the process's device) run a one-pass kernel that reads every
  * id once: its workgroups (as many as the GPU holds resident at once) meet
  * at one grid-wide barrier.  The three-kernel path (count, scan, scatter)
  * is launched behind it and returns at once when the one-pass kernel has
  * written the outputs; it does the work instead when the offsets are not
  * ordinary, or when the barrier gave up (about 30-60 ms of waiting, when
- * other work on the GPU keeps workgroups from being resident).  Both give
+ * other work on the GPU keeps workgroups from being resident).  All give
  * the same outputs.  The environment variable EB_BUCKETIZE_ONE_PASS (read on
- * every call) forces the choice: 0 never, 1 whenever the kernel can hold
- * the batch (up to 16 destinations and about 23 million ids).
+ * every call) forces the choice: 0 the three kernels, 1 the one-pass kernel
+ * whenever it can hold the batch (up to 16 destinations and about 23 million
+ * ids), else the three.
  *
  * No allocation, no host synchronisation; calls that overlap on the same
  * workspace race.  out_offsets, out_indices, segments and the workspace must

@@ -18,8 +18,9 @@
 // contraction); eb_sum_partials is bound by it, eb_bucketize by its waves'
 // chains of dependent loads and by instruction issue.
 //
-// eb_bucketize runs, for batches of at least kOneMinIds ids and at most 16
-// destinations, a one-pass kernel that reads every id once (see "One-pass
+// eb_bucketize runs batches of fewer than kOneMinIds ids and at most 64
+// destinations as two kernels ("Two-kernel bucketize", eb_bucketize_two.h), and
+// larger ones of at most 16 destinations as a one-pass kernel that reads every id once (see "One-pass
 // bucketize" below), followed by the three kernels here, which return at
 // once when it has written the outputs and otherwise do the work; every
 // other batch takes the three kernels alone (eb_bucketize_ex the same with
@@ -1388,6 +1389,8 @@ __global__ __launch_bounds__(kBlock) void eb_bucket_scatter(const BucketArgs a)
     }
 }
 
+#include "eb_bucketize_two.h"
+
 // out[j] = sum over s of partials[s*n + j] (then / L of its bag for mean).
 struct PartialArgs {
     const float *partials;
@@ -2303,6 +2306,73 @@ bool one_pass_fits(int32_t T, int64_t B, int32_t G, int64_t nnz, hipStream_t st)
     return one_pass_chunks(nnz, (int64_t)blocks * kOneWaves, T) <= kOneChunks;
 }
 
+// Destinations the two-kernel path's instantiation for G ranks.
+int two_owners(int G) { return G <= 8 ? 8 : G <= 16 ? 16 : G <= 32 ? 32 : 64; }
+
+// The two-kernel path's shape: even runs of a table's bags per workgroup, a
+// whole table at most.  Three workgroups per compute unit are resident
+// together and a fourth would start late (26 tables x 2048 int32 bags into 8
+// blocks, 500 / 640 / 754 / 1196 workgroups: 25.1 / 24.0 / 22.5 / 23.1 us); a
+// small batch takes fewer, about 640 ids each (8 tables x 1024 bags of 40
+// ids, 64 / 256 / 512 workgroups: 17.0 / 10.5 / 10.4 us).  The workspace may
+// hold fewer still.
+struct TwoShape {
+    int32_t bags, groups_per_table;
+    int64_t groups;
+};
+
+constexpr int64_t kTwoMaxGroups = 3 * 256;
+constexpr int64_t kTwoGroupIds = 640;
+
+size_t two_group_bytes(int G) { return (size_t)two_owners(G) * (sizeof(int64_t) + kTwoWaves * sizeof(uint32_t)); }
+
+TwoShape two_shape(int32_t T, int64_t B, int32_t G, int64_t nnz, size_t workspace_bytes)
+{
+    TwoShape s;
+    const int64_t target = std::min({nnz / kTwoGroupIds, kTwoMaxGroups, (int64_t)(workspace_bytes / two_group_bytes(G))});
+    const int64_t per_table = std::max<int64_t>(1, target / T);
+    s.bags = (int32_t)std::min<int64_t>((B + per_table - 1) / per_table, kTwoMaxBags);
+    s.groups_per_table = (int32_t)std::min<int64_t>((B + s.bags - 1) / s.bags, kTwoMaxGroups + 1);
+    s.groups = (int64_t)T * s.groups_per_table;
+    return s;
+}
+
+// Whether a batch takes the two-kernel path: up to 64 destinations, few
+// enough workgroups, and fewer ids than those beyond which reading them twice
+// costs more than the three kernels' launches (26 tables of skewed int64 ids,
+// three kernels against this path, us: 3.9 M ids into 8 blocks 38.1 against
+// 29.4, into 16 45.9 against 36.0, into 32 / 64 64.9 / 81.3 against 51.6 /
+// 74.7; 5.3 M into 32 / 64 76.3 / 95.6 against 69.1 / 109.7).  Where the
+// one-pass kernel runs it stays: at 4 to 6 M ids it is up to 20% slower than
+// this path, but its waves split any bag, while here one long bag is left to
+// the four waves of its workgroup (in the three kernels, to one wave).
+// The loads need the offsets and bounds 4-byte and the workspace 16-byte
+// aligned.  EB_BUCKETIZE_ONE_PASS set to 0 or 1 leaves the path out.
+bool two_fits(const TwoShape &s, int32_t G, int64_t nnz, const void *offsets, const void *bounds, const void *workspace,
+              size_t workspace_bytes)
+{
+    if (G > kTwoMaxOwners || s.groups > kTwoMaxGroups || one_pass_setting() >= 0) return false;
+    if (nnz < 1 || nnz >= (G > kTreeShards && G <= 32 ? (int64_t)5 << 20 : kOneMinIds)) return false;
+    if ((uintptr_t)offsets % 4 || (uintptr_t)bounds % 4 || (uintptr_t)workspace % 16) return false;
+    return (size_t)s.groups * two_group_bytes(G) <= workspace_bytes;
+}
+
+template <typename IT>
+hipError_t launch_two(const TwoArgs &a, int64_t groups, hipStream_t st)
+{
+    void *args[] = {(void *)&a};
+    const void *totals, *place;
+    switch (two_owners(a.G)) {
+    case 8: totals = (const void *)eb_two_totals<IT, 8>, place = (const void *)eb_two_place<IT, 8>; break;
+    case 16: totals = (const void *)eb_two_totals<IT, 16>, place = (const void *)eb_two_place<IT, 16>; break;
+    case 32: totals = (const void *)eb_two_totals<IT, 32>, place = (const void *)eb_two_place<IT, 32>; break;
+    default: totals = (const void *)eb_two_totals<IT, 64>, place = (const void *)eb_two_place<IT, 64>; break;
+    }
+    hipError_t err = hipLaunchKernel(totals, dim3((unsigned)groups), dim3(kTwoBlock), args, 0, st);
+    if (err == hipSuccess) err = hipLaunchKernel(place, dim3((unsigned)groups), dim3(kTwoBlock), args, 0, st);
+    return err;
+}
+
 size_t classic_workspace_bytes(int32_t T, int64_t B, int32_t G)
 {
     return ((size_t)workspace_entries(T, B, G) * sizeof(int64_t) + 255) / 256 * 256;
@@ -2345,6 +2415,30 @@ int bucketize_impl(int32_t T, int64_t B, int32_t G, const int64_t *bounds, int32
     if (workspace_bytes < need || (need > 0 && !workspace))
         return fail(EB_ERR_INVALID, "eb_bucketize: workspace smaller than eb_bucketize_workspace reports");
     hipStream_t st = (hipStream_t)stream;
+
+    const TwoShape two = TB > 0 ? two_shape(T, B, G, nnz, need) : TwoShape{};
+    if (TB > 0 && two_fits(two, G, nnz, offsets, bounds, workspace, need)) {
+        TwoArgs ta;
+        std::memset(&ta, 0, sizeof ta);
+        ta.bounds = bounds;
+        ta.indices = indices;
+        ta.offsets = offsets;
+        ta.out_offsets = out_offsets;
+        ta.out_indices = out_indices;
+        ta.segments = segments;
+        ta.group_totals = (int64_t *)workspace;
+        ta.wave_before = (uint32_t *)(ta.group_totals + two.groups * two_owners(G));
+        ta.out_cap = out_capacity;
+        ta.nnz = nnz;
+        ta.B = B;
+        ta.TB = TB;
+        ta.G = G;
+        ta.bags = two.bags;
+        ta.groups_per_table = two.groups_per_table;
+        const hipError_t err = i32 ? launch_two<int32_t>(ta, two.groups, st) : launch_two<int64_t>(ta, two.groups, st);
+        if (err != hipSuccess) return fail(EB_ERR_HIP, "eb_bucketize: %s", hipGetErrorString(err));
+        return EB_OK;
+    }
 
     BucketArgs ba;
     std::memset(&ba, 0, sizeof ba);
