@@ -169,6 +169,20 @@ def _same_device(dev, *tensors) -> None:
             raise ValueError(f"tensor on {x.device}, expected {dev}")
 
 
+def _stream_ptr(stream, dev) -> int:
+    """The hipStream_t of ``stream``, or of ``dev``'s current stream.  The
+    latter without a torch Stream object where torch offers that (0.1 us
+    against 1.9)."""
+    if stream is not None:
+        return stream.cuda_stream
+    import torch
+
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if raw is None or dev.index is None:
+        return torch.cuda.current_stream(dev).cuda_stream
+    return raw(dev.index)
+
+
 def bucketize(bounds, indices, offsets, T: int, B: int, stream=None, capacity=None):
     """Torch convenience for eb_bucketize / eb_bucketize_ex.  ``bounds``:
     int64 device [T, G+1]; ``indices`` and ``offsets`` both int64 or both
@@ -195,11 +209,9 @@ def bucketize(bounds, indices, offsets, T: int, B: int, stream=None, capacity=No
     seg = torch.empty(G + 1, dtype=torch.int64, device=dev)
     nbytes = eb_bucketize_workspace(T, B, G)
     ws = torch.empty(max(1, nbytes), dtype=torch.uint8, device=dev)
-    if stream is None:
-        stream = torch.cuda.current_stream(dev)
     eb_bucketize_ex(T, B, G, bounds.data_ptr(), itype, indices.data_ptr() if indices.numel() else None,
                     indices.numel(), offsets.data_ptr(), out_off.data_ptr(), out_idx.data_ptr(), cap,
-                    seg.data_ptr(), ws.data_ptr(), nbytes, stream.cuda_stream)
+                    seg.data_ptr(), ws.data_ptr(), nbytes, _stream_ptr(stream, dev))
     return out_off, out_idx, seg, ws
 
 
@@ -223,11 +235,9 @@ def sum_partials(partials, B: int, T: int, D: int, mean_offsets=None, nnz: int =
     if mean_offsets is not None and (mean_offsets.dtype != torch.int64 or not mean_offsets.is_contiguous() or
                                      mean_offsets.numel() != T * B + 1):
         raise ValueError("mean_offsets must be contiguous int64 [T*B+1]")
-    if stream is None:
-        stream = torch.cuda.current_stream(partials.device)
     eb_sum_partials(G, partials.data_ptr(), B, T, D,
                     None if mean_offsets is None else mean_offsets.data_ptr(), nnz,
-                    out.data_ptr(), stream.cuda_stream)
+                    out.data_ptr(), _stream_ptr(stream, partials.device))
     return out
 
 
@@ -235,12 +245,12 @@ def _index_type(indices, offsets) -> int:
     """EB_IDX_I64 / EB_IDX_I32 from two contiguous tensors of one integer type."""
     import torch
 
-    codes = {torch.int64: EB_IDX_I64, torch.int32: EB_IDX_I32}
-    if indices.dtype not in codes or offsets.dtype != indices.dtype:
+    dt = indices.dtype
+    if (dt != torch.int64 and dt != torch.int32) or offsets.dtype != dt:
         raise ValueError("indices and offsets must both be int64 or both int32")
     if not (indices.is_contiguous() and offsets.is_contiguous()):
         raise ValueError("indices / offsets must be contiguous")
-    return codes[indices.dtype]
+    return EB_IDX_I64 if dt == torch.int64 else EB_IDX_I32
 
 
 _TORCH_DTYPE_CODES = {"torch.float32": EB_F32, "torch.float16": EB_F16, "torch.bfloat16": EB_BF16}
@@ -250,7 +260,7 @@ class EmbeddingBagTables:
     """Tables held as torch device tensors [stored_rows, D] of one dtype."""
 
     def __init__(self, tables, rows=None, shard_lo: int = 0, shard_hi: int = INT64_MAX):
-        import torch  # noqa: F401  (device memory and streams only)
+        import torch
 
         self.tables = list(tables)
         if not self.tables:
@@ -269,8 +279,19 @@ class EmbeddingBagTables:
         self.stored_rows = [int(w.shape[0]) for w in self.tables]
         self.rows = list(rows) if rows is not None else [shard_lo + n for n in self.stored_rows]
         self.shard_lo, self.shard_hi = int(shard_lo), int(shard_hi)
+        self._rows_arg = (None, None)
+        self._fp32 = t0.new_empty(0, dtype=torch.float32)  # outputs are made from it (1.0 us against torch.empty's 1.7)
         self.handle = eb_create_tables([w.data_ptr() for w in self.tables], self.stored_rows,
                                        self.D, self.dtype)
+
+    def _rows_array(self):
+        """``rows`` as the C array the calls take, built again only when the
+        list's values have changed (64 tables: 2.3 us)."""
+        seen, arr = self._rows_arg
+        if seen != self.rows:
+            arr = _i64_array(self.rows)
+            self._rows_arg = (list(self.rows), arr)
+        return arr
 
     def forward(self, indices, offsets, B: int, mode: int = EB_SUM, out=None, hits=None,
                 stream=None):
@@ -280,12 +301,10 @@ class EmbeddingBagTables:
 
         dev = self.tables[0].device
         if out is None:
-            out = torch.empty((B, self.T * self.D), dtype=torch.float32, device=dev)
+            out = self._fp32.new_empty((B, self.T * self.D))
         want_hits = hits is not None and hits is not False
         if hits is True:
             hits = torch.empty((B, self.T), dtype=torch.int32, device=dev)
-        if stream is None:
-            stream = torch.cuda.current_stream(dev)
         for tnsr, dt in ((indices, torch.int64), (offsets, torch.int64)):
             if tnsr.dtype != dt or not tnsr.is_contiguous():
                 raise ValueError("indices / offsets must be contiguous int64")
@@ -296,9 +315,10 @@ class EmbeddingBagTables:
         if want_hits and (hits.dtype != torch.int32 or not hits.is_contiguous() or hits.numel() < B * self.T):
             raise ValueError("hits must be contiguous int32 [B, T]")
         _same_device(dev, indices, offsets, out, hits if want_hits else None)
-        eb_forward(self.handle, self.T, self.rows, self.D, self.dtype, indices.data_ptr(),
-                   indices.numel(), offsets.data_ptr(), B, mode, self.shard_lo, self.shard_hi,
-                   out.data_ptr(), hits.data_ptr() if want_hits else None, stream.cuda_stream)
+        _check(library().eb_forward(self.handle, self.T, self._rows_array(), self.D, self.dtype, indices.data_ptr() or None,
+                                    indices.numel(), offsets.data_ptr(), B, mode, self.shard_lo, self.shard_hi,
+                                    out.data_ptr() or None, (hits.data_ptr() or None) if want_hits else None,
+                                    _stream_ptr(stream, dev) or None))
         return (out, hits) if want_hits else out
 
     def forward_ex(self, indices, offsets, B: int, mode: int = EB_SUM, out=None, out_cols=None,
@@ -315,7 +335,7 @@ class EmbeddingBagTables:
         dev = self.tables[0].device
         itype = _index_type(indices, offsets)
         if out is None:
-            out = torch.empty((B, self.T * self.D), dtype=torch.float32, device=dev)
+            out = self._fp32.new_empty((B, self.T * self.D))
         # The library writes rows of unit column stride, whatever B is.
         if out.dtype != torch.float32 or out.dim() != 2 or out.shape[0] != B or \
                 (out.shape[1] > 1 and out.stride(1) != 1):
@@ -325,8 +345,10 @@ class EmbeddingBagTables:
             raise ValueError("hits must be int32 [B, >= T] with unit column stride")
         if offsets.numel() != self.T * B + 1:
             raise ValueError("offsets must have T*B+1 entries")
-        cols = [t * self.D for t in range(self.T)] if out_cols is None else list(out_cols)
-        if len(cols) != self.T or any(c < 0 or c + self.D > out.shape[1] for c in cols):
+        # No columns given: the library's own default, table t at column t*D.
+        cols = None if out_cols is None else list(out_cols)
+        if self.T * self.D > out.shape[1] if cols is None else \
+                len(cols) != self.T or any(c < 0 or c + self.D > out.shape[1] for c in cols):
             raise ValueError("out_cols must give T columns with c + D <= out.shape[1]")
         if hits is not None and hits.shape[1] < self.T:
             raise ValueError("hits must be int32 [B, >= T]")
@@ -334,16 +356,15 @@ class EmbeddingBagTables:
                                     weights.numel() != indices.numel()):
             raise ValueError("weights must be contiguous fp32 with one entry per index")
         _same_device(dev, indices, offsets, out, hits, weights)
-        if stream is None:
-            stream = torch.cuda.current_stream(dev)
         ldo = out.stride(0) if B > 1 else out.shape[1]
         ldh = (hits.stride(0) if B > 1 else hits.shape[1]) if hits is not None else 0
-        eb_forward_ex(self.handle, self.T, self.rows, self.D, self.dtype, itype, indices.data_ptr(),
-                      indices.numel(), offsets.data_ptr(),
-                      weights.data_ptr() if weights is not None and weights.numel() else None,
-                      B, mode, self.shard_lo, self.shard_hi,
-                      out.data_ptr(), ldo, cols,
-                      hits.data_ptr() if hits is not None else None, ldh, stream.cuda_stream)
+        _check(library().eb_forward_ex(self.handle, self.T, self._rows_array(), self.D, self.dtype, itype,
+                                       indices.data_ptr() or None, indices.numel(), offsets.data_ptr(),
+                                       weights.data_ptr() if weights is not None and weights.numel() else None,
+                                       B, mode, self.shard_lo, self.shard_hi, out.data_ptr() or None, ldo,
+                                       None if cols is None else _i64_array(cols),
+                                       (hits.data_ptr() or None) if hits is not None else None, ldh,
+                                       _stream_ptr(stream, dev) or None))
         return (out, hits) if hits is not None else out
 
     def prepare(self, indices, offsets, B: int, mode: int, out, hits=None, stream=None, weights=None):
@@ -352,8 +373,7 @@ class EmbeddingBagTables:
         (on ``stream``) each time it is invoked."""
         import torch
 
-        if stream is None:
-            stream = torch.cuda.current_stream(self.tables[0].device)
+        stream_ptr = _stream_ptr(stream, self.tables[0].device)
         if offsets.numel() != self.T * B + 1 or out.numel() < B * self.T * self.D:
             raise ValueError("offsets / out do not match T, B, D")
         if out.dtype != torch.float32 or not out.is_contiguous():
@@ -372,14 +392,14 @@ class EmbeddingBagTables:
             fn = lib.eb_forward
             args = (self.handle, self.T, _i64_array(self.rows), self.D, self.dtype,
                     indices.data_ptr(), indices.numel(), offsets.data_ptr(), B, mode, self.shard_lo,
-                    self.shard_hi, out.data_ptr(), hits_ptr, stream.cuda_stream)
+                    self.shard_hi, out.data_ptr(), hits_ptr, stream_ptr)
         else:
             fn = lib.eb_forward_ex
             args = (self.handle, self.T, _i64_array(self.rows), self.D, self.dtype, itype,
                     indices.data_ptr(), indices.numel(), offsets.data_ptr(),
                     weights.data_ptr() if weights is not None else None, B, mode, self.shard_lo,
                     self.shard_hi, out.data_ptr(), self.T * self.D, None, hits_ptr, self.T,
-                    stream.cuda_stream)
+                    stream_ptr)
         keep = (indices, offsets, out, hits, weights)
 
         def call():
