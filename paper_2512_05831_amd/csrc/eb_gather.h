@@ -830,9 +830,11 @@ inline bool wave_fits(int64_t rb, int dtype, const GatherBuffers &buf)
 //     32 ids: 21.5 / 32.2 / 59.0 against 25.0 / 31.2 / 47.4; 512-B rows, 4 / 8
 //     / 16 ids: 24.6 / 36.4 / 62.4 against 26.9 / 36.0 / 52.1; 1-KB rows, 2 / 4
 //     / 8 ids: 30.6 / 42.2 / 68.5 against 34.2 / 41.7 / 60.4; 64-B rows, 32 /
-//     64 ids: 24.3 / 47.4 against 27.9 / 42.2).  Streamed rows are bound by
-//     HBM: those of 16-byte chunks keep the teams, as do rows under 128 B (24-B
-//     rows, 60 uniform ids: 65.4 against 72.1).
+//     64 ids: 24.3 / 47.4 against 27.9 / 42.2).  Under the hint rows of 128 B
+//     and more in 16-byte chunks are bound by HBM and keep the teams, as do
+//     rows under 64 B (64 uniform ids of 32 B in 100 K / 1 M rows: 30.0 / 75.9
+//     against 32.3 / 76.1; of 64 B: 43.4 / 86.5 against 42.0 / 82.5; of 96 B:
+//     76.0 / 133.0 against 73.8 / 126.3).
 //   * 16-byte rows of more than 2 KB stay with the teams (8-KB rows, 2048 bags
 //     of 100 ids: 253 against 283).
 inline bool use_wave(int64_t rb, int cb, const Shape &whole, bool hint, int64_t bags, int64_t nnz)
@@ -843,7 +845,7 @@ inline bool use_wave(int64_t rb, int cb, const Shape &whole, bool hint, int64_t 
     const int R = whole.R, P = kWave / R;
     const bool stream = hint && rb >= 128;
     if (bags <= kWaveSlots && (nnz >= 2 * P * bags || (rb >= 256 && !(stream && R == 32)))) return true;
-    if (hint && (cb == 16 || rb < 128)) return false;
+    if (hint && (rb < 64 || (rb >= 128 && cb == 16))) return false;
     return nnz >= (int64_t)(4 * P < kWave ? 4 * P : kWave) * bags;
 }
 
@@ -874,10 +876,15 @@ inline GatherPlan plan_gather(int32_t D, int32_t dtype, const GatherBuffers &buf
     const bool fits = wave_fits(rb, dtype, buf);
     const Shape whole = team_shape(fits ? (int)((rb + 15) / 16 * 16) : 16, 16, true, false); // a wave per bag
     if (fits && use_wave(rb, cb, whole, hint, T * B, nnz)) {
+        // Each XCD a run of workgroups under the hint, as with teams (16 x 4096
+        // bags of 60 uniform ids of 100 fp16: 242 against 205 us, 64 ids of 32
+        // bf16 in 100 K rows: 58 against 42), but not in small batches, where
+        // finding the run costs 0.3 us.
         plan.fn = pick_wave_kernel(weighted, i32, dtype, whole.R, whole.C, hint && rb >= 128);
         plan.chunk_bytes = 16;
         plan.split = split_waves(T * B, nnz, rb, dtype);
         plan.bags_per_block = plan.split > 1 ? 1 : kWavesPerBlock;
+        plan.xcd_runs = hint && T * B > kFewBagsMax;
         return plan;
     }
     plan.team = cb > 0;

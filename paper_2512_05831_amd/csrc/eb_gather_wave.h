@@ -125,9 +125,15 @@ __global__ __launch_bounds__(kWave *kMaxSplit) void eb_gather_wave(const GatherA
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
     const int g = lane / R, rl = lane % R;
-    const int t = blockIdx.y;
+    int t = blockIdx.y, block = blockIdx.x;
+    if (a.xcd_runs) { // workgroups go to the XCDs in turn: each takes a run of them
+        const int n = gridDim.x * gridDim.y, i = t * gridDim.x + block, x = i % kXcds;
+        const int lb = x * (n / kXcds) + min(x, n % kXcds) + i / kXcds;
+        t = lb / (int)gridDim.x;
+        block = lb - t * (int)gridDim.x;
+    }
     const int split = a.split;
-    const int64_t b = a.bag_begin + (split > 1 ? (int64_t)blockIdx.x : (int64_t)blockIdx.x * kWavesPerBlock + wave);
+    const int64_t b = a.bag_begin + (split > 1 ? (int64_t)block : (int64_t)block * kWavesPerBlock + wave);
     if (b >= a.B) return; // never a part of a split bag's workgroup
 
     const IT *o = (const IT *)a.offsets + (int64_t)t * a.B + b;
