@@ -48,7 +48,7 @@ METRIC = "pooled lookups/sec + effective HBM GB/s (% of MI355X peak) per config"
 HBM_PEAK_GBPS = 8000.0
 # the gather kernels and the host code that shapes their launches (the C ABI's
 # argument checks in eb.hip do not change what runs)
-KERNEL_SRCS = [os.path.join(ROOT, "paper_2512_05831_amd", "csrc", "eb_gather.h")]
+KERNEL_SRCS = [os.path.join(ROOT, "paper_2512_05831_amd", "csrc", f) for f in ("eb_gather.h", "eb_gather_wave.h")]
 PROFILES = os.path.join(ROOT, "profiles")
 
 
