@@ -288,8 +288,8 @@ struct __align__(16) TwoRecord {
     int32_t pad;
 };
 
-// Out-of-order offsets: wave w takes its share of the bags one at a time, with
-// 64-bit slots (overlapping bags may send more ids than there are).
+// Where offsets are out of order: wave w takes its share of the bags one at a
+// time, with 64-bit slots (overlapping bags may send more ids than there are).
 template <typename IT, int kOwners>
 __device__ void two_place_bags(const TwoArgs &a, const TwoOwners<kOwners> &owners, const TwoGroup<IT> &v, const TwoStarts &st,
                                int w, int lane, int64_t segment, int64_t slot)
@@ -378,7 +378,10 @@ __global__ __launch_bounds__(kTwoBlock) void eb_two_place(const TwoArgs a)
         if (lane == G - 1) a.segments[G] = upto;
     }
     const Owners owners(kOwners > 8 ? bnd : v.bnd, G, lane);
-    const bool ordered = two_ordered(st, lane);
+    // Other workgroups' overlapping bags may send more ids than the batch holds,
+    // which moves this one's positions past 32 bits although its own offsets
+    // are in order: it then takes its bags one at a time too.
+    const bool ordered = two_ordered(st, lane) && readlane64(upto, kWave - 1) <= kTwoMaxIds;
     if (!ordered) {
         // Bags may overlap, so a wave's share may exceed what wave_before
         // holds: count again.
@@ -395,8 +398,8 @@ __global__ __launch_bounds__(kTwoBlock) void eb_two_place(const TwoArgs a)
         two_place_bags<IT>(a, owners, v, st, wave, lane, segment, segment + first);
         return;
     }
-    // Ordered: at most nnz <= kTwoMaxIds ids are sent, so 32 bits hold every
-    // position, and every byte offset into out_indices.
+    // At most kTwoMaxIds ids are sent, so 32 bits hold every position, and every
+    // byte offset into out_indices.
     int slot = (int)(segment + first), start = slot;
     const uint32_t cap = (uint32_t)min<int64_t>(a.out_cap, kTwoMaxIds);
     const int64_t row = a.TB + 1;

@@ -72,6 +72,26 @@ def test_disordered_offsets(G, kind, device):
     check_bucketize(T, B, idx, off, even_bounds([5000] * T, G), device)
 
 
+@pytest.mark.parametrize("itype", [torch.int64, torch.int32])
+def test_more_ids_than_32_bits_before_ordered_bags(itype, device):
+    """2048 bags that each send the whole batch put the ordered bags behind them
+    at positions past 2^32: none of their ids may land in out_indices."""
+    nnz, repeats, tail = 1 << 21, 2048, 4096
+    gen = torch.Generator(device=device).manual_seed(3)
+    idx = torch.randint(0, 5000, (nnz,), generator=gen, device=device).to(itype)
+    step = nnz // 2 // tail
+    off = torch.cat([torch.tensor([0, nnz], device=device).repeat(repeats),
+                     nnz // 2 + step * torch.arange(tail + 1, device=device)])
+    lengths = (off[1:] - off[:-1]).clamp(min=0)
+    want = torch.cat([lengths.new_zeros(1), lengths.cumsum(0)])
+    assert int(want[-1]) > 1 << 32
+    bounds = torch.tensor([[0, 5000, 5000]], device=device)
+    out_off, out_idx, seg = eb.bucketize(bounds, idx, off.to(itype), 1, off.numel() - 1, capacity=nnz)[:3]
+    assert seg.tolist() == [0, int(want[-1]), int(want[-1])]
+    assert torch.equal(out_off[0], want) and not out_off[1].any()
+    assert torch.equal(out_idx[:nnz], idx)
+
+
 def test_bounds_and_ids_at_the_type_limits(device):
     hi, lo = np.iinfo(np.int64).max, np.iinfo(np.int64).min
     idx = np.array([lo, -1, 0, 5, hi - 1, hi, lo + 1, 5], dtype=np.int64)
