@@ -288,9 +288,10 @@ class EmbeddingBagTables:
         """``rows`` as the C array the calls take, built again only when the
         list's values have changed (64 tables: 2.3 us)."""
         seen, arr = self._rows_arg
-        if seen != self.rows:
-            arr = _i64_array(self.rows)
-            self._rows_arg = (list(self.rows), arr)
+        rows = self.rows if type(self.rows) is list else list(self.rows)
+        if seen != rows:
+            arr = _i64_array(rows)
+            self._rows_arg = (list(rows), arr)
         return arr
 
     def forward(self, indices, offsets, B: int, mode: int = EB_SUM, out=None, hits=None,
