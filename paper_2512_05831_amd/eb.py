@@ -11,6 +11,7 @@ the current HIP stream.
 from __future__ import annotations
 
 import ctypes
+import operator
 import os
 
 from . import build as _build
@@ -292,6 +293,8 @@ class EmbeddingBagTables:
         if seen != rows:
             arr = _i64_array(rows)
             self._rows_arg = (list(rows), arr)
+        else:
+            operator.index(sum(rows))  # equal floats are refused, as building the array refuses them
         return arr
 
     def forward(self, indices, offsets, B: int, mode: int = EB_SUM, out=None, hits=None,

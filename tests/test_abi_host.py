@@ -355,3 +355,20 @@ def test_torch_helpers_refuse_host_tensors():
     p = torch.zeros((2, 3, 8), dtype=torch.float32)
     with pytest.raises(ValueError, match="device"):
         eb.sum_partials(p, 3, 1, 8)
+
+
+def test_rows_of_tables_stay_whole_numbers():
+    """The row counts' C array is kept between calls, which lets no value pass
+    that building it refuses: floats equal to the counts seen before."""
+    import numpy as np
+    et = object.__new__(eb.EmbeddingBagTables)
+    et._rows_arg = (None, None)
+    for rows in ([3, 4], [3, 4], np.array([3, 5]), (3, 5), [3, np.int32(5)]):
+        et.rows = rows
+        assert list(et._rows_array()) == [int(r) for r in rows]
+    for rows in ([3.0, 5], [3, 5.0], (3.0, 5.0), np.array([3.0, 5.0])):
+        et.rows = rows
+        with pytest.raises(TypeError):
+            et._rows_array()
+    et.rows = [3, 5]
+    assert list(et._rows_array()) == [3, 5]
