@@ -280,12 +280,12 @@ __global__ __launch_bounds__(kTwoBlock) void eb_two_totals(const TwoArgs a)
 }
 
 // What a pass leaves of each of its chunks for the bags that start in it, per
-// destination: the lanes whose id goes there, and the wave's ids for it before
-// the chunk.
+// destination: the lanes whose id goes there, and the ids for it before the
+// chunk (all of them: the lanes that read it may be the only active ones, so
+// nothing is fetched from the destination's own lane then).
 struct __align__(16) TwoRecord {
     uint32_t own_lo, own_hi;
-    int32_t before;
-    int32_t pad;
+    int64_t before;
 };
 
 // Where offsets are out of order: wave w takes its share of the bags one at a
@@ -423,7 +423,7 @@ __global__ __launch_bounds__(kTwoBlock) void eb_two_place(const TwoArgs a)
             owners.template split<true>((int64_t)id[u], lanes_below(R - u * kWave), valid, own, owner4, rank);
             const int base = __builtin_amdgcn_ds_bpermute(owner4, slot);
             if (lane_bit(valid)) pos[u] = (uint32_t)(base + rank);
-            if (lane < kOwners) rec[u][lane] = TwoRecord{(uint32_t)own, (uint32_t)(own >> 32), slot - start, 0};
+            if (lane < kOwners) rec[u][lane] = TwoRecord{(uint32_t)own, (uint32_t)(own >> 32), first + (slot - start)};
             slot += __popcll(own);
         }
         // The bags that start in the pass, a lane each.
@@ -437,8 +437,8 @@ __global__ __launch_bounds__(kTwoBlock) void eb_two_place(const TwoArgs a)
                 const TwoRecord *r = rec[rel / kWave];
                 for (int g = 0; g < G; ++g) {
                     const TwoRecord x = r[g];
-                    const int n = x.before + __popc(x.own_lo & (uint32_t)below) + __popc(x.own_hi & (uint32_t)(below >> 32));
-                    out_off[(int64_t)g * row + j + lane] = readlane64(first, g) + n;
+                    const int n = __popc(x.own_lo & (uint32_t)below) + __popc(x.own_hi & (uint32_t)(below >> 32));
+                    out_off[(int64_t)g * row + j + lane] = x.before + n;
                 }
             }
             j += (int)__popcll(here);
