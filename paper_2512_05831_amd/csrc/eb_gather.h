@@ -599,6 +599,28 @@ constexpr int groups_per_bag(int R, bool few, bool single)
 
 using KernelFn = void (*)(GatherArgs);
 
+// Most waves a bag of the wave kernel can have: the partial sums of `chunks`
+// 16-byte chunks a wave stay within 32 KB of LDS.
+constexpr int split_limit(int64_t chunks, int dtype)
+{
+    const int64_t wave_lds = chunks * (16 / (dtype == EB_F32 ? 4 : 2)) * (int64_t)sizeof(float);
+    int split = 1;
+    while (split < kMaxSplit && 2 * split * wave_lds <= 32768) split *= 2;
+    return split;
+}
+
+// Most waves in a workgroup of the wave kernel's instance with C chunks per
+// lane: its narrowest row's split, at least the unsplit call's waves.  One
+// bound of 16 waves for every instance left those of 7 and 8 half-precision
+// chunks 128 registers and up to 168 bytes of scratch per lane (25 tables x
+// 4000 bags of 2 ids of 4075 fp16: 981 us, 587 without; 54 x 701 bags of 10 ids
+// of 3700 bf16: 573 and 366; the plain kernel: 1492 and 1490).
+constexpr int wave_block(int C, int dtype)
+{
+    const int split = split_limit(C > 1 ? (C - 1) * kWave + 1 : 1, dtype);
+    return split > kWavesPerBlock ? split : kWavesPerBlock;
+}
+
 // Rows in flight per lane: streamed (non-temporal) rows of 128 B and more all
 // go to HBM, where two per lane saturate the random-read rate and more only
 // queue; narrower rows need more requests per byte in flight, and cached rows
@@ -858,11 +880,9 @@ inline bool use_wave(int64_t rb, int cb, const Shape &whole, bool hint, int64_t 
 // 28.2 / 30.5; the team kernel: 5.6, 49.4, 14.2, 28.4).
 inline int split_waves(int64_t bags, int64_t nnz, int64_t rb, int dtype)
 {
-    const int64_t wave_lds = (rb + 15) / 16 * (16 / elem_bytes(dtype)) * (int64_t)sizeof(float);
+    const int limit = split_limit((rb + 15) / 16, dtype);
     int split = 1;
-    while (split < kMaxSplit && 2 * bags * split <= kWaveSlots / 2 && nnz >= 48 * split * bags &&
-           2 * split * wave_lds <= 32768)
-        split *= 2;
+    while (split < limit && 2 * bags * split <= kWaveSlots / 2 && nnz >= 48 * split * bags) split *= 2;
     return split;
 }
 

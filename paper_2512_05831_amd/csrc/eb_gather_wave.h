@@ -110,16 +110,17 @@ constexpr int wave_unroll(int R, int C)
 // windows of 64 ids in turn; their partial sums meet in LDS
 // (a.split * chunks * 16 bytes' worth of floats, dynamic).
 template <typename IT, int DT, int R, int C, bool kW, bool kStream>
-__global__ __launch_bounds__(kWave *kMaxSplit) void eb_gather_wave(const GatherArgs a)
+__global__ __launch_bounds__(kWave *wave_block(C, DT)) void eb_gather_wave(const GatherArgs a)
 {
     constexpr int P = kWave / R;
     constexpr int U = wave_unroll(R, C);
     constexpr int kEs = DT == EB_F32 ? 4 : 2;
     constexpr int kEpc = 16 / kEs;
     static_assert(U * P <= kWave, "a pass stays within the window");
-    __shared__ uint32_t stage[kMaxSplit][kWave];
-    __shared__ float wstage[kW ? kMaxSplit : 1][kWave];
-    __shared__ int wave_hits[kMaxSplit];
+    constexpr int kWaves = wave_block(C, DT);
+    __shared__ uint32_t stage[kWaves][kWave];
+    __shared__ float wstage[kW ? kWaves : 1][kWave];
+    __shared__ int wave_hits[kWaves];
     extern __shared__ float partial[];
 
     const int lane = threadIdx.x & (kWave - 1);
