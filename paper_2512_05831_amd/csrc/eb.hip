@@ -185,6 +185,7 @@ int forward_impl(const char *who, const eb_tables *h, int32_t T, const int64_t *
     if (hits && (ldh < T || B > kMax / ldh)) return fail(EB_ERR_INVALID, "%s: bad ldh (must be >= T with B*ldh in int64)", who);
 
     int64_t most_rows = 0;
+    double all_local = 0;
     for (int32_t t = 0; t < T; ++t) {
         if (rows[t] < 0) return fail(EB_ERR_INVALID, "%s: negative rows[t]", who);
         const int64_t n = local_rows(rows[t], shard_lo, shard_hi);
@@ -194,15 +195,17 @@ int forward_impl(const char *who, const eb_tables *h, int32_t T, const int64_t *
         if ((uint64_t)n > kMaxLocalRows)
             return fail(EB_ERR_UNSUPPORTED, "%s: more than 4294967294 gatherable rows in a table", who);
         most_rows = std::max(most_rows, n);
+        all_local += (double)n;
     }
 
     // Vector stores need every (bag, table) output row start aligned to them.
     int out_align = std::min(pow2_align((uintptr_t)out), pow2_align((uintptr_t)ldo * 4));
     for (int32_t t = 0; t < T; ++t)
         out_align = std::min(out_align, pow2_align((uintptr_t)out_col(out_cols, t, D) * 4));
-    const GatherBuffers buffers{h->align, out_align, pow2_align((uintptr_t)offsets), most_rows};
-    const GatherPlan plan = plan_gather(D, dtype, buffers, index_type == EB_IDX_I32, weights != nullptr, T, B, nnz, mode);
-    if (!plan.fn) return fail(EB_ERR_UNSUPPORTED, "%s: no kernel for this row shape", who);
+    const GatherBuffers buffers{h->align, out_align, pow2_align((uintptr_t)offsets), most_rows, all_local};
+    const GatherRoute plan = choose_route(D, dtype, buffers, T, B, nnz, mode);
+    const KernelFn fn = route_kernel(plan, dtype, index_type == EB_IDX_I32, weights != nullptr);
+    if (!fn) return fail(EB_ERR_UNSUPPORTED, "%s: no kernel for this row shape", who);
 
     GatherArgs a;
     std::memset(&a, 0, sizeof a);
@@ -233,7 +236,7 @@ int forward_impl(const char *who, const eb_tables *h, int32_t T, const int64_t *
         }
         a.offsets = (const char *)offsets + (size_t)t0 * B * ies;
         a.hits = hits ? hits + t0 : nullptr;
-        const hipError_t err = launch_gather(plan, a, nt, dtype, (hipStream_t)stream);
+        const hipError_t err = launch_gather(fn, plan, a, nt, dtype, (hipStream_t)stream);
         if (err != hipSuccess) return fail(EB_ERR_HIP, "%s: kernel launch failed: %s", who, hipGetErrorString(err));
     }
     return EB_OK;
@@ -312,6 +315,15 @@ int eb_forward_ex(const eb_tables *h, int32_t T, const int64_t *rows, int32_t D,
     } catch (...) {
         return eb_detail::unexpected_exception("eb_forward_ex");
     }
+}
+
+int eb_gather_route(const eb_route_call *call, eb_route *route)
+{
+    const GatherBuffers buffers{call->table_align, call->out_align, call->offsets_align, call->local_rows,
+                                (double)call->T * (double)call->local_rows};
+    const GatherRoute r = choose_route(call->D, call->dtype, buffers, call->T, call->B, call->nnz, call->mode);
+    *route = eb_route{r.kernel, r.chunk_bytes, r.R, r.C, r.few, r.single, r.stream, r.xcd_runs, r.split};
+    return 0;
 }
 
 } // extern "C"

@@ -9,6 +9,7 @@
 #include <stdint.h>
 
 #include "../../include/eb.h"
+#include "../../include/eb_route.h"
 
 namespace eb_gather {
 
@@ -761,6 +762,8 @@ struct Shape {
 // single-GPU shapes: up to 1.5x faster, never slower).
 constexpr int64_t kWaveSlots = 256 * 32;
 constexpr int64_t kFewBagsMax = 2048;
+constexpr int64_t kXcdTableBytes = (int64_t)32 << 20; // the XCDs' L2s together
+constexpr double kStreamTableBytes = 2e9;               // eight times the last-level cache
 
 inline int rows_in_flight_per_bag(const Shape &s, bool stream)
 {
@@ -787,22 +790,26 @@ inline Shape team_shape(int rb, int cb, bool few, bool single, bool narrow512 = 
     return s;
 }
 
-// The kernel of a call and how its bags map to workgroups.
-struct GatherPlan {
-    KernelFn fn;
-    bool team;           // team kernel (else plain)
-    int bags_per_block;
+// How a call's bags map to workgroups, and the kernel's template arguments.
+struct GatherRoute {
+    int32_t kernel;      // EB_ROUTE_*
+    int32_t chunk_bytes; // bytes of a row one lane loads at a time (0: plain kernel)
+    int32_t R, C;        // lanes per row, chunks per lane
+    bool few;            // team kernel: small-batch mapping
+    bool single;         // team kernel: one lane group per bag
+    bool stream;         // non-temporal row loads
     bool xcd_runs;       // each XCD takes a contiguous run of workgroups
-    int chunk_bytes;     // bytes of a row one lane loads at a time (0: plain kernel)
-    int split;           // wave kernel: waves per bag (0: team or plain kernel)
+    int32_t split;       // wave kernel: waves per bag (0: team or plain kernel)
+    int32_t bags_per_block;
 };
 
-// What a call's buffers allow (host side of plan_gather).
+// What a call's buffers allow.
 struct GatherBuffers {
     int table_align;      // largest power of two up to 16 dividing every table pointer
     int out_align;        // ... every output row start in bytes
     int offsets_align;    // ... the offsets pointer
     int64_t local_rows;   // most gatherable rows of a table
+    double all_local;     // gatherable rows of all tables
 };
 
 // Chunk size of the team kernel for rows of rb bytes, or 0 for the plain
@@ -886,38 +893,52 @@ inline int split_waves(int64_t bags, int64_t nnz, int64_t rb, int dtype)
     return split;
 }
 
-inline GatherPlan plan_gather(int32_t D, int32_t dtype, const GatherBuffers &buf, bool i32, bool weighted,
-                              int64_t T, int64_t B, int64_t nnz, int32_t mode)
+inline GatherRoute choose_route(int32_t D, int32_t dtype, const GatherBuffers &buf, int64_t T, int64_t B, int64_t nnz,
+                                int32_t mode)
 {
-    GatherPlan plan{nullptr, false, kWavesPerBlock, false, 0, 0};
+    GatherRoute route{EB_ROUTE_PLAIN, 0, 0, 0, false, false, false, false, 0, kWavesPerBlock};
     const int64_t rb = (int64_t)D * elem_bytes(dtype);
     const int cb = chunk_bytes(rb, dtype, buf.table_align, buf.out_align);
     const bool hint = (mode & EB_HINT_STREAM_ROWS) != 0;
+    const int64_t bags = T * B;
     const bool fits = wave_fits(rb, dtype, buf);
     const Shape whole = team_shape(fits ? (int)((rb + 15) / 16 * 16) : 16, 16, true, false); // a wave per bag
-    if (fits && use_wave(rb, cb, whole, hint, T * B, nnz)) {
-        // Each XCD a run of workgroups under the hint, as with teams (16 x 4096
-        // bags of 60 uniform ids of 100 fp16: 242 against 205 us, 64 ids of 32
-        // bf16 in 100 K rows: 58 against 42), but not in small batches, where
-        // finding the run costs 0.3 us.
-        plan.fn = pick_wave_kernel(weighted, i32, dtype, whole.R, whole.C, hint && rb >= 128);
-        plan.chunk_bytes = 16;
-        plan.split = split_waves(T * B, nnz, rb, dtype);
-        plan.bags_per_block = plan.split > 1 ? 1 : kWavesPerBlock;
-        plan.xcd_runs = hint && T * B > kFewBagsMax;
-        return plan;
+    if (fits && use_wave(rb, cb, whole, hint, bags, nnz)) {
+        route.kernel = EB_ROUTE_WAVE;
+        route.chunk_bytes = 16;
+        route.R = whole.R;
+        route.C = whole.C;
+        // Non-temporal loads for rows of whole 16-byte chunks.  The others'
+        // pieces cross cache lines, which are then asked for twice, so they
+        // are only streamed where hardly any row comes back: the tables hold
+        // 2 GB and more and a row in ten or fewer is used.  Non-temporal
+        // against cached: 8 tables of 875 K rows x 763 bags of 35 ids of 242
+        // fp32 (3% used) 46.5 against 52.4 us; 9 tables of 720 K rows x 10272
+        // bags of 47 ids of 227 fp32 (0.67 uses a row) 752 against 658, the
+        // plain kernel 664; 38 tables of 11 K rows x 7880 bags of 14 ids of 217
+        // fp32 (10 uses) 690, 392 and 403.
+        route.stream = hint && rb >= 128 &&
+                       (cb == 16 || (buf.all_local * rb >= kStreamTableBytes && nnz <= buf.all_local / 10));
+        route.split = split_waves(bags, nnz, rb, dtype);
+        route.bags_per_block = route.split > 1 ? 1 : kWavesPerBlock;
+        // Each XCD a run of workgroups under the hint, as with teams (64 ids of
+        // 32 bf16 in 100 K rows: 58 against 42), but not in small batches,
+        // where finding the run costs 0.3 us, nor where eight tables at a time
+        // would push each other's reused rows out of the caches: cached loads
+        // from tables of over 32 MB, a row in four or more used (0.67 uses a
+        // row, above: 776 against 658; tables of 11 K rows, above: 346 against
+        // 392; 4 tables x 34679 bags of 15 ids of 228 fp16, a row in
+        // twelve used: 153 against 165).
+        route.xcd_runs = hint && bags > kFewBagsMax &&
+                         (cb == 16 || buf.local_rows * rb <= kXcdTableBytes || nnz <= buf.all_local / 4);
+        return route;
     }
-    plan.team = cb > 0;
-    plan.chunk_bytes = cb;
-    if (!plan.team) {
-        plan.fn = weighted ? pick_weighted_kernel(i32, dtype, false, 0, 0, false, false, false)
-                           : pick_kernel<false>(i32, dtype, false, 0, 0, false, false, false);
-        return plan;
-    }
+    if (cb == 0) return route;
+    route.kernel = EB_ROUTE_TEAM;
+    route.chunk_bytes = cb;
     // Non-temporal loads lose for rows narrower than 128 bytes.
     const bool stream = hint && rb >= 128;
     const Shape normal = team_shape((int)rb, cb, false, false);
-    const int64_t bags = T * B;
     const int64_t waves = bags / (kWave / (normal.R * normal.P));
     const bool few = waves < kWaveSlots && bags <= kFewBagsMax &&
                      nnz > 2 * (int64_t)rows_in_flight_per_bag(normal, stream) * bags;
@@ -934,18 +955,28 @@ inline GatherPlan plan_gather(int32_t D, int32_t dtype, const GatherBuffers &buf
     const bool single = (stream || short_bags) && !few && narrow_team < normal.R * normal.P &&
                         bags / (kWave / narrow_team) >= kWaveSlots / 2;
     const Shape sh = few ? team_shape((int)rb, cb, true, false) : single ? narrow : normal;
-    if (cb == 16)
-        plan.fn = weighted ? pick_weighted_kernel(i32, dtype, true, sh.R, sh.C, stream, few, single)
-                           : pick_kernel<false>(i32, dtype, true, sh.R, sh.C, stream, few, single);
-    else
-        plan.fn = pick_narrow_kernel(weighted, i32, dtype, cb, sh.R, stream, few, single);
-    plan.bags_per_block = (kWave / (sh.R * sh.P)) * kWavesPerBlock;
+    route.R = sh.R;
+    route.C = sh.C;
+    route.few = few;
+    route.single = single;
+    route.stream = stream;
+    route.bags_per_block = (kWave / (sh.R * sh.P)) * kWavesPerBlock;
     // No reuse: each XCD takes a contiguous run of bags (measured faster for
     // uniform ids, also for rows under 128 B).  Otherwise hardware order, so
     // all XCDs work on the same table at once and its hot rows share the
     // last-level cache.
-    plan.xcd_runs = hint;
-    return plan;
+    route.xcd_runs = hint;
+    return route;
+}
+
+inline KernelFn route_kernel(const GatherRoute &r, int32_t dtype, bool i32, bool weighted)
+{
+    if (r.kernel == EB_ROUTE_WAVE) return pick_wave_kernel(weighted, i32, dtype, r.R, r.C, r.stream);
+    if (r.kernel == EB_ROUTE_TEAM && r.chunk_bytes < 16)
+        return pick_narrow_kernel(weighted, i32, dtype, r.chunk_bytes, r.R, r.stream, r.few, r.single);
+    const bool team = r.kernel == EB_ROUTE_TEAM;
+    return weighted ? pick_weighted_kernel(i32, dtype, team, r.R, r.C, r.stream, r.few, r.single)
+                    : pick_kernel<false>(i32, dtype, team, r.R, r.C, r.stream, r.few, r.single);
 }
 
 // LDS for the partial sums of a split bag.
@@ -957,7 +988,7 @@ inline size_t split_lds_bytes(int split, int chunks, int dtype)
 // Launch one piece of at most 64 tables (a.base / nlocal / col / offsets /
 // hits already set for it), in as many launches as the grid bound needs:
 // each launch covers a range of every table's bags.
-inline hipError_t launch_gather(const GatherPlan &plan, GatherArgs &a, int32_t nt, int dtype, hipStream_t stream)
+inline hipError_t launch_gather(KernelFn fn, const GatherRoute &plan, GatherArgs &a, int32_t nt, int dtype, hipStream_t stream)
 {
     const int64_t kMaxBlocks = (int64_t)1 << 22;
     const int64_t blocks_all_bags = (a.B + plan.bags_per_block - 1) / plan.bags_per_block;
@@ -970,7 +1001,7 @@ inline hipError_t launch_gather(const GatherPlan &plan, GatherArgs &a, int32_t n
         if (plan.split > 0) {
             a.split = plan.split;
             void *wargs[] = {&a};
-            const hipError_t err = hipLaunchKernel((const void *)plan.fn, dim3((unsigned)bpt, (unsigned)nt),
+            const hipError_t err = hipLaunchKernel((const void *)fn, dim3((unsigned)bpt, (unsigned)nt),
                                                    dim3(plan.split > 1 ? kWave * plan.split : kBlock), wargs,
                                                    split_lds_bytes(plan.split, a.chunks, dtype), stream);
             if (err != hipSuccess) return err;
@@ -978,7 +1009,7 @@ inline hipError_t launch_gather(const GatherPlan &plan, GatherArgs &a, int32_t n
         }
         const int64_t grid = plan.xcd_runs ? (a.nblocks + kXcds - 1) / kXcds * kXcds : a.nblocks;
         void *args[] = {&a};
-        const hipError_t err = hipLaunchKernel((const void *)plan.fn, dim3((unsigned)grid), dim3(kBlock), args, 0, stream);
+        const hipError_t err = hipLaunchKernel((const void *)fn, dim3((unsigned)grid), dim3(kBlock), args, 0, stream);
         if (err != hipSuccess) return err;
     }
     return hipSuccess;

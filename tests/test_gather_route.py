@@ -1,0 +1,44 @@
+"""Which kernel a pooled lookup takes: the library's choice, on the host."""
+import ctypes
+
+from paper_2512_05831_amd import eb
+
+PLAIN, TEAM, WAVE = 0, 1, 2
+
+
+class Call(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_int32) for n in ("D", "dtype", "weighted", "mode", "table_align", "out_align",
+                                              "offsets_align", "reserved")] + \
+               [(n, ctypes.c_int64) for n in ("T", "B", "nnz", "table_rows", "local_rows")]
+
+
+class Route(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_int32) for n in ("kernel", "chunk_bytes", "lanes", "chunks", "small_batch", "narrow",
+                                              "non_temporal", "xcd_runs", "split")]
+
+
+def route(D, dtype, T, B, ids, rows, local=None, hint=False, weighted=False, align=16):
+    """The route of T x B bags of `ids` ids on average."""
+    call = Call(D=D, dtype=dtype, weighted=weighted, mode=eb.EB_HINT_STREAM_ROWS if hint else 0, table_align=align,
+                out_align=align, offsets_align=16, T=T, B=B, nnz=int(T * B * ids), table_rows=rows,
+                local_rows=rows if local is None else local)
+    r = Route()
+    assert eb.library().eb_gather_route(ctypes.byref(call), ctypes.byref(r)) == 0
+    return r
+
+
+def test_hinted_rows_no_16_byte_chunk_divides_are_cached():
+    """Such rows share cache lines, and a batch may name them again: the hint
+    moves neither their loads past the caches nor, where tables that do not fit
+    the L2s are reused, eight tables' rows into the caches at a time.  Only
+    where tables far beyond the caches see hardly a row twice are they streamed."""
+    for D, dtype in ((227, eb.EB_F32), (217, eb.EB_F32), (257, eb.EB_F16), (236, eb.EB_BF16)):
+        r = route(D, dtype, 9, 10272, 47, 720_000, hint=True)
+        assert (r.kernel, r.non_temporal, r.xcd_runs) == (WAVE, 0, 0), D
+        r = route(D, dtype, 38, 7880, 14, 11_000, hint=True)
+        assert (r.kernel, r.non_temporal, r.xcd_runs) == (WAVE, 0, 1), D
+        for rows, nt in ((2_000_000, 0), (4_000_000, 1)):  # a row in 6 used, in 12
+            r = route(D, dtype, 4, 34679, 10, rows, hint=True)
+            assert (r.kernel, r.non_temporal, r.xcd_runs) == (WAVE, nt, 1), (D, rows)
+    r = route(128, eb.EB_F32, 8, 2048, 40, 1_000_000, hint=True)  # whole 16-byte chunks: streamed, by teams
+    assert (r.kernel, r.non_temporal, r.xcd_runs) == (TEAM, 1, 1)
