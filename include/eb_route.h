@@ -17,11 +17,10 @@ enum { EB_ROUTE_PLAIN = 0, EB_ROUTE_TEAM = 1, EB_ROUTE_WAVE = 2 };
 
 /* One eb_forward / eb_forward_ex call, as the choice of its kernel sees it. */
 typedef struct eb_route_call {
-    int32_t D, dtype, weighted, mode;
+    int32_t D, dtype, mode;
     int32_t table_align;   /* largest power of two up to 16 dividing every table pointer, */
     int32_t out_align;     /* every output row start in bytes, */
     int32_t offsets_align; /* and the offsets pointer */
-    int32_t reserved;
     int64_t T, B, nnz;
     int64_t table_rows;    /* rows of every table, */
     int64_t local_rows;    /* and how many of them can be gathered here */

@@ -185,7 +185,7 @@ int forward_impl(const char *who, const eb_tables *h, int32_t T, const int64_t *
     if (hits && (ldh < T || B > kMax / ldh)) return fail(EB_ERR_INVALID, "%s: bad ldh (must be >= T with B*ldh in int64)", who);
 
     int64_t most_rows = 0;
-    double all_local = 0;
+    double all_local = 0, all_rows = 0;
     for (int32_t t = 0; t < T; ++t) {
         if (rows[t] < 0) return fail(EB_ERR_INVALID, "%s: negative rows[t]", who);
         const int64_t n = local_rows(rows[t], shard_lo, shard_hi);
@@ -196,13 +196,14 @@ int forward_impl(const char *who, const eb_tables *h, int32_t T, const int64_t *
             return fail(EB_ERR_UNSUPPORTED, "%s: more than 4294967294 gatherable rows in a table", who);
         most_rows = std::max(most_rows, n);
         all_local += (double)n;
+        all_rows += (double)rows[t];
     }
 
     // Vector stores need every (bag, table) output row start aligned to them.
     int out_align = std::min(pow2_align((uintptr_t)out), pow2_align((uintptr_t)ldo * 4));
     for (int32_t t = 0; t < T; ++t)
         out_align = std::min(out_align, pow2_align((uintptr_t)out_col(out_cols, t, D) * 4));
-    const GatherBuffers buffers{h->align, out_align, pow2_align((uintptr_t)offsets), most_rows, all_local};
+    const GatherBuffers buffers{h->align, out_align, pow2_align((uintptr_t)offsets), most_rows, all_local, all_rows};
     const GatherRoute plan = choose_route(D, dtype, buffers, T, B, nnz, mode);
     const KernelFn fn = route_kernel(plan, dtype, index_type == EB_IDX_I32, weights != nullptr);
     if (!fn) return fail(EB_ERR_UNSUPPORTED, "%s: no kernel for this row shape", who);
@@ -320,7 +321,7 @@ int eb_forward_ex(const eb_tables *h, int32_t T, const int64_t *rows, int32_t D,
 int eb_gather_route(const eb_route_call *call, eb_route *route)
 {
     const GatherBuffers buffers{call->table_align, call->out_align, call->offsets_align, call->local_rows,
-                                (double)call->T * (double)call->local_rows};
+                                (double)call->T * (double)call->local_rows, (double)call->T * (double)call->table_rows};
     const GatherRoute r = choose_route(call->D, call->dtype, buffers, call->T, call->B, call->nnz, call->mode);
     *route = eb_route{r.kernel, r.chunk_bytes, r.R, r.C, r.few, r.single, r.stream, r.xcd_runs, r.split};
     return 0;

@@ -810,6 +810,7 @@ struct GatherBuffers {
     int offsets_align;    // ... the offsets pointer
     int64_t local_rows;   // most gatherable rows of a table
     double all_local;     // gatherable rows of all tables
+    double all_rows;      // rows of all tables
 };
 
 // Chunk size of the team kernel for rows of rb bytes, or 0 for the plain
@@ -839,43 +840,56 @@ inline bool wave_fits(int64_t rb, int dtype, const GatherBuffers &buf)
            buf.offsets_align >= 4 && buf.local_rows <= (int64_t)(0xFFFFFFFFu / (uint64_t)rb);
 }
 
-// Whether a call takes the wave kernel rather than a team or plain kernel.
-// A wave per bag costs a large batch of short bags more waves than a team per
-// bag does, and gains from cheaper loads as bags grow.  P = 64 / R rows are
-// read at a time; all times in us, team or plain kernel against wave kernel,
-// kernel traces:
-//   * rows no aligned chunk fits: always (16 tables x 4096 bags of 20 ids of
-//     189 fp16: 306 against 90, of 1 id: 42.6 against 30.3).
-//   * small batches, where the chain of dependent loads is the time: always up
-//     to 2048 bags (8 x 256 bags of 16 ids of 64 fp32: 4.8 against 4.0; one bag
-//     of 1 id in 32: 4.2 against 3.8); up to 8192 when a bag fills two passes
-//     or rows have 256 bytes or more (64 x 128 bags of 64 fp32, 1 id: 6.0
-//     against 4.6, 16 ids: 10.2 against 8.6; of 32 fp32, 4 ids: 4.4 against
-//     4.9, 16 ids: 6.8 against 6.4), except streamed 512-byte rows in shorter
-//     bags (1 id: 5.1 against 5.6).
-//   * cached or ragged rows: bags of four passes on average, at most a window
-//     (16 x 4096 bags, skewed ids: 128-B rows, 16 ids: 20.7 against 23.5, 32
-//     ids: 35.3 against 30.1, 64 ids: 67.7 against 45.6; 256-B rows, 8 / 16 /
-//     32 ids: 21.5 / 32.2 / 59.0 against 25.0 / 31.2 / 47.4; 512-B rows, 4 / 8
-//     / 16 ids: 24.6 / 36.4 / 62.4 against 26.9 / 36.0 / 52.1; 1-KB rows, 2 / 4
-//     / 8 ids: 30.6 / 42.2 / 68.5 against 34.2 / 41.7 / 60.4; 64-B rows, 32 /
-//     64 ids: 24.3 / 47.4 against 27.9 / 42.2).  Under the hint rows of 128 B
-//     and more in 16-byte chunks are bound by HBM and keep the teams, as do
-//     rows under 64 B (64 uniform ids of 32 B in 100 K / 1 M rows: 30.0 / 75.9
-//     against 32.3 / 76.1; of 64 B: 43.4 / 86.5 against 42.0 / 82.5; of 96 B:
-//     76.0 / 133.0 against 73.8 / 126.3).
-//   * 16-byte rows of more than 2 KB stay with the teams (8-KB rows, 2048 bags
-//     of 100 ids: 253 against 283).
-inline bool use_wave(int64_t rb, int cb, const Shape &whole, bool hint, int64_t bags, int64_t nnz)
+// Whether a call takes the wave kernel rather than a team or plain kernel,
+// given the lanes a team kernel would put on a bag and the ids expected in the
+// gatherable rows (of a row block, its share of the bags' ids).  P = 64 / R rows
+// are read at a time; all times in us, team or plain kernel against wave kernel.
+//   * rows no aligned chunk fits: yes (16 tables x 4096 bags of 20 ids of 189
+//     fp16: 306 against 90, of 1 id: 42.6 against 30.3; 4 x 50899 bags of 2 ids
+//     of 253 fp32, a sixteenth gathered: 118 against 79).
+//   * rows of more than 2 KB in 16-byte chunks: no (8-KB rows, 2048 bags of 100
+//     ids: 253 against 283).
+//   * up to 2048 bags, where the chain of dependent loads is the time: yes (8 x
+//     256 bags of 16 ids of 64 fp32: 4.8 against 4.0; one bag of 1 id in 32:
+//     4.2 against 3.8).
+//   * over 8192 bags under the hint: not rows of 128 B and more in 16-byte
+//     chunks, which are bound by HBM, nor rows under 64 B (64 uniform ids of
+//     32 B in 100 K / 1 M rows: 30.0 / 75.9 against 32.3 / 76.1; of 64 B: 43.4
+//     / 86.5 against 42.0 / 82.5; of 96 B: 76.0 / 133.0 against 73.8 / 126.3).
+//   * where a team would be a whole wave as well: yes, its loads cost less and
+//     need no predicates (some 700 random shapes: 1.25 times the speed, 0.93
+//     at worst; 2 x 28103 weighted bags of 27 ids of 256 B, an eighth gathered:
+//     41.4 against 23.4).
+//   * where it would be less, a wave per bag costs more waves: from four
+//     gathered passes, at most a window (16 x 4096 bags, skewed ids: 128-B
+//     rows, 16 / 32 / 64 ids: 20.7 / 35.3 / 67.7 against 23.5 / 30.1 / 45.6;
+//     256-B rows, 8 / 16 / 32 ids: 21.5 / 32.2 / 59.0 against 25.0 / 31.2 /
+//     47.4; 512-B rows, 4 / 8 / 16 ids: 24.6 / 36.4 / 62.4 against 26.9 / 36.0
+//     / 52.1; 1-KB rows, 2 / 4 / 8 ids: 30.6 / 42.2 / 68.5 against 34.2 / 41.7
+//     / 60.4; 64-B rows, 32 / 64 ids: 24.3 / 47.4 against 27.9 / 42.2), with
+//     and without weights.  At four to five passes bags of one length may lose
+//     and ragged ones gain (18 x 7169 weighted bags of 20 ids of 256 B: 45.4
+//     against 52.3; 49 x 620 of 1 to 45: 31.0 against 25.6); over 131072 bags,
+//     where ragged ones even out, both lose (12 shapes: 0.93 to 1.08 times the
+//     speed ragged, 0.88 to 0.96 of one length): from five there.  Ids that a
+//     row block does not hold cost no passes (2 x 55087 bags of 17 ids of 256 B, a
+//     sixteenth gathered: 22.6 against 37.5; 2 x 24038 of 49 ids of 128 B, a
+//     quarter gathered: 15.5 against 22.8).
+//   * up to 8192 bags, rows up to 128 B: from two passes, gathered or not (64 x
+//     128 bags of 32 fp32, 4 ids: 4.4 against 4.9, 16 ids: 6.8 against 6.4; 2 x
+//     1088 bags of 29 ids of 128 B, a quarter gathered: 6.4 against 3.9).
+inline bool use_wave(int64_t rb, int cb, const Shape &whole, int team_lanes, bool hint, int64_t bags, int64_t nnz,
+                     double gathered)
 {
     if (cb == 0) return true;
     if (cb == 16 && whole.C > 2) return false;
     if (bags <= kFewBagsMax) return true;
-    const int R = whole.R, P = kWave / R;
-    const bool stream = hint && rb >= 128;
-    if (bags <= kWaveSlots && (nnz >= 2 * P * bags || (rb >= 256 && !(stream && R == 32)))) return true;
-    if (hint && (rb < 64 || (rb >= 128 && cb == 16))) return false;
-    return nnz >= (int64_t)(4 * P < kWave ? 4 * P : kWave) * bags;
+    if (bags > kWaveSlots && hint && (rb < 64 || (rb >= 128 && cb == 16))) return false;
+    if (team_lanes == kWave) return true;
+    const int P = kWave / whole.R;
+    if (bags <= kWaveSlots && nnz >= 2 * P * bags) return true;
+    const int ids = (bags > 16 * kWaveSlots ? 5 : 4) * P;
+    return gathered >= (double)(ids < kWave ? ids : kWave) * (double)bags;
 }
 
 // Waves per bag of the wave kernel, a power of two: more than one when a bag
@@ -893,49 +907,10 @@ inline int split_waves(int64_t bags, int64_t nnz, int64_t rb, int dtype)
     return split;
 }
 
-inline GatherRoute choose_route(int32_t D, int32_t dtype, const GatherBuffers &buf, int64_t T, int64_t B, int64_t nnz,
-                                int32_t mode)
+// The team kernel's mapping for rows of rb bytes in chunks of cb bytes.
+inline GatherRoute team_route(int64_t rb, int cb, bool hint, int64_t bags, int64_t nnz)
 {
-    GatherRoute route{EB_ROUTE_PLAIN, 0, 0, 0, false, false, false, false, 0, kWavesPerBlock};
-    const int64_t rb = (int64_t)D * elem_bytes(dtype);
-    const int cb = chunk_bytes(rb, dtype, buf.table_align, buf.out_align);
-    const bool hint = (mode & EB_HINT_STREAM_ROWS) != 0;
-    const int64_t bags = T * B;
-    const bool fits = wave_fits(rb, dtype, buf);
-    const Shape whole = team_shape(fits ? (int)((rb + 15) / 16 * 16) : 16, 16, true, false); // a wave per bag
-    if (fits && use_wave(rb, cb, whole, hint, bags, nnz)) {
-        route.kernel = EB_ROUTE_WAVE;
-        route.chunk_bytes = 16;
-        route.R = whole.R;
-        route.C = whole.C;
-        // Non-temporal loads for rows of whole 16-byte chunks.  The others'
-        // pieces cross cache lines, which are then asked for twice, so they
-        // are only streamed where hardly any row comes back: the tables hold
-        // 2 GB and more and a row in ten or fewer is used.  Non-temporal
-        // against cached: 8 tables of 875 K rows x 763 bags of 35 ids of 242
-        // fp32 (3% used) 46.5 against 52.4 us; 9 tables of 720 K rows x 10272
-        // bags of 47 ids of 227 fp32 (0.67 uses a row) 752 against 658, the
-        // plain kernel 664; 38 tables of 11 K rows x 7880 bags of 14 ids of 217
-        // fp32 (10 uses) 690, 392 and 403.
-        route.stream = hint && rb >= 128 &&
-                       (cb == 16 || (buf.all_local * rb >= kStreamTableBytes && nnz <= buf.all_local / 10));
-        route.split = split_waves(bags, nnz, rb, dtype);
-        route.bags_per_block = route.split > 1 ? 1 : kWavesPerBlock;
-        // Each XCD a run of workgroups under the hint, as with teams (64 ids of
-        // 32 bf16 in 100 K rows: 58 against 42), but not in small batches,
-        // where finding the run costs 0.3 us, nor where eight tables at a time
-        // would push each other's reused rows out of the caches: cached loads
-        // from tables of over 32 MB, a row in four or more used (0.67 uses a
-        // row, above: 776 against 658; tables of 11 K rows, above: 346 against
-        // 392; 4 tables x 34679 bags of 15 ids of 228 fp16, a row in
-        // twelve used: 153 against 165).
-        route.xcd_runs = hint && bags > kFewBagsMax &&
-                         (cb == 16 || buf.local_rows * rb <= kXcdTableBytes || nnz <= buf.all_local / 4);
-        return route;
-    }
-    if (cb == 0) return route;
-    route.kernel = EB_ROUTE_TEAM;
-    route.chunk_bytes = cb;
+    GatherRoute route{EB_ROUTE_TEAM, cb, 0, 0, false, false, false, false, 0, 0};
     // Non-temporal loads lose for rows narrower than 128 bytes.
     const bool stream = hint && rb >= 128;
     const Shape normal = team_shape((int)rb, cb, false, false);
@@ -966,6 +941,47 @@ inline GatherRoute choose_route(int32_t D, int32_t dtype, const GatherBuffers &b
     // all XCDs work on the same table at once and its hot rows share the
     // last-level cache.
     route.xcd_runs = hint;
+    return route;
+}
+
+inline GatherRoute choose_route(int32_t D, int32_t dtype, const GatherBuffers &buf, int64_t T, int64_t B, int64_t nnz,
+                                int32_t mode)
+{
+    const int64_t rb = (int64_t)D * elem_bytes(dtype);
+    const int cb = chunk_bytes(rb, dtype, buf.table_align, buf.out_align);
+    const bool hint = (mode & EB_HINT_STREAM_ROWS) != 0;
+    const int64_t bags = T * B;
+    GatherRoute route = cb > 0 ? team_route(rb, cb, hint, bags, nnz)
+                               : GatherRoute{EB_ROUTE_PLAIN, 0, 0, 0, false, false, false, false, 0, kWavesPerBlock};
+    const int team_lanes = kWavesPerBlock * kWave / route.bags_per_block;
+    const bool fits = wave_fits(rb, dtype, buf);
+    const Shape whole = team_shape(fits ? (int)((rb + 15) / 16 * 16) : 16, 16, true, false); // a wave per bag
+    const double gathered = buf.all_rows > 0 ? (double)nnz * (buf.all_local / buf.all_rows) : 0;
+    if (!fits || !use_wave(rb, cb, whole, team_lanes, hint, bags, nnz, gathered)) return route;
+    route = GatherRoute{EB_ROUTE_WAVE, 16, whole.R, whole.C, false, false, false, false, 0, kWavesPerBlock};
+    // Non-temporal loads for rows of whole 16-byte chunks.  The others'
+    // pieces cross cache lines, which are then asked for twice, so they
+    // are only streamed where hardly any row comes back: the tables hold
+    // 2 GB and more and a row in ten or fewer is used.  Non-temporal
+    // against cached: 8 tables of 875 K rows x 763 bags of 35 ids of 242
+    // fp32 (3% used) 46.5 against 52.4 us; 9 tables of 720 K rows x 10272
+    // bags of 47 ids of 227 fp32 (0.67 uses a row) 752 against 658, the
+    // plain kernel 664; 38 tables of 11 K rows x 7880 bags of 14 ids of 217
+    // fp32 (10 uses) 690, 392 and 403.
+    route.stream = hint && rb >= 128 &&
+                   (cb == 16 || (buf.all_local * rb >= kStreamTableBytes && gathered <= buf.all_local / 10));
+    route.split = split_waves(bags, nnz, rb, dtype);
+    route.bags_per_block = route.split > 1 ? 1 : kWavesPerBlock;
+    // Each XCD a run of workgroups under the hint, as with teams (64 ids of
+    // 32 bf16 in 100 K rows: 58 against 42), but not in small batches,
+    // where finding the run costs 0.3 us, nor where eight tables at a time
+    // would push each other's reused rows out of the caches: cached loads
+    // from tables of over 32 MB, a row in four or more used (0.67 uses a
+    // row, above: 776 against 658; tables of 11 K rows, above: 346 against
+    // 392; 4 tables x 34679 bags of 15 ids of 228 fp16, a row in
+    // twelve used: 153 against 165).
+    route.xcd_runs = hint && bags > kFewBagsMax &&
+                     (cb == 16 || buf.local_rows * rb <= kXcdTableBytes || gathered <= buf.all_local / 4);
     return route;
 }
 

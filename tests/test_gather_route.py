@@ -7,8 +7,8 @@ PLAIN, TEAM, WAVE = 0, 1, 2
 
 
 class Call(ctypes.Structure):
-    _fields_ = [(n, ctypes.c_int32) for n in ("D", "dtype", "weighted", "mode", "table_align", "out_align",
-                                              "offsets_align", "reserved")] + \
+    _fields_ = [(n, ctypes.c_int32) for n in ("D", "dtype", "mode", "table_align", "out_align",
+                                              "offsets_align")] + \
                [(n, ctypes.c_int64) for n in ("T", "B", "nnz", "table_rows", "local_rows")]
 
 
@@ -17,9 +17,9 @@ class Route(ctypes.Structure):
                                               "non_temporal", "xcd_runs", "split")]
 
 
-def route(D, dtype, T, B, ids, rows, local=None, hint=False, weighted=False, align=16):
+def route(D, dtype, T, B, ids, rows, local=None, hint=False, align=16):
     """The route of T x B bags of `ids` ids on average."""
-    call = Call(D=D, dtype=dtype, weighted=weighted, mode=eb.EB_HINT_STREAM_ROWS if hint else 0, table_align=align,
+    call = Call(D=D, dtype=dtype, mode=eb.EB_HINT_STREAM_ROWS if hint else 0, table_align=align,
                 out_align=align, offsets_align=16, T=T, B=B, nnz=int(T * B * ids), table_rows=rows,
                 local_rows=rows if local is None else local)
     r = Route()
@@ -42,3 +42,27 @@ def test_hinted_rows_no_16_byte_chunk_divides_are_cached():
             assert (r.kernel, r.non_temporal, r.xcd_runs) == (WAVE, nt, 1), (D, rows)
     r = route(128, eb.EB_F32, 8, 2048, 40, 1_000_000, hint=True)  # whole 16-byte chunks: streamed, by teams
     assert (r.kernel, r.non_temporal, r.xcd_runs) == (TEAM, 1, 1)
+
+
+def test_large_batches_take_the_wave_kernel_where_a_team_is_a_wave_too():
+    """Bags that teams narrower than a wave would take go to the wave kernel
+    from four passes, by the ids a row block gathers and not by those its bags
+    name; up to 8192 bags from two, gathered or not."""
+    for D, dtype, four, full in ((64, eb.EB_F32, 16, 24), (128, eb.EB_F32, 8, 12), (256, eb.EB_BF16, 8, 12),
+                                 (256, eb.EB_F32, 4, 6)):
+        assert route(D, dtype, 2, 55087, four - 1, 1_000_000).kernel == TEAM
+        assert route(D, dtype, 2, 55087, four, 1_000_000).kernel == WAVE
+        assert route(D, dtype, 2, 55087, full - 1, 1_000_000, local=125_000).kernel == TEAM
+        assert route(D, dtype, 2, 55087, full, 1_000_000, local=125_000).kernel == WAVE
+        assert route(D, dtype, 2, 55087, full, 1_000_000, hint=True).kernel == TEAM
+        assert route(D, dtype, 2, 4000, 1, 1_000_000, hint=True).kernel == WAVE
+    for D, dtype, four in ((64, eb.EB_F16, 32), (32, eb.EB_F32, 32), (16, eb.EB_F32, 64), (8, eb.EB_F16, 64)):
+        assert route(D, dtype, 2, 55087, four - 1, 1_000_000).kernel == TEAM
+        assert route(D, dtype, 2, 55087, four, 1_000_000).kernel == WAVE
+        assert route(D, dtype, 2, 55087, 4 * four - 1, 1_000_000, local=250_000).kernel == TEAM
+        assert route(D, dtype, 2, 55087, 4 * four, 1_000_000, local=250_000).kernel == WAVE
+        assert route(D, dtype, 4, 40000, four, 1_000_000).kernel == (TEAM if four < 64 else WAVE)  # five there
+        assert route(D, dtype, 4, 40000, min(64, four * 5 // 4), 1_000_000).kernel == WAVE
+    assert route(64, eb.EB_F16, 2, 4000, 16, 1_000_000, local=250_000).kernel == WAVE
+    assert route(64, eb.EB_F16, 2, 4000, 15, 1_000_000).kernel == TEAM
+    assert route(64, eb.EB_F16, 2, 55087, 100, 0).kernel == TEAM  # no rows at all
