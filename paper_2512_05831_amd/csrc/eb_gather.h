@@ -959,29 +959,36 @@ inline GatherRoute choose_route(int32_t D, int32_t dtype, const GatherBuffers &b
     const double gathered = buf.all_rows > 0 ? (double)nnz * (buf.all_local / buf.all_rows) : 0;
     if (!fits || !use_wave(rb, cb, whole, team_lanes, hint, bags, nnz, gathered)) return route;
     route = GatherRoute{EB_ROUTE_WAVE, 16, whole.R, whole.C, false, false, false, false, 0, kWavesPerBlock};
-    // Non-temporal loads for rows of whole 16-byte chunks.  The others'
-    // pieces cross cache lines, which are then asked for twice, so they
-    // are only streamed where hardly any row comes back: the tables hold
-    // 2 GB and more and a row in ten or fewer is used.  Non-temporal
-    // against cached: 8 tables of 875 K rows x 763 bags of 35 ids of 242
-    // fp32 (3% used) 46.5 against 52.4 us; 9 tables of 720 K rows x 10272
-    // bags of 47 ids of 227 fp32 (0.67 uses a row) 752 against 658, the
+    // Streamed only where hardly any row comes back: the tables hold 2 GB and
+    // more and a row in ten or fewer is used.  Non-temporal against cached: 8
+    // tables of 875 K rows x 763 bags of 35 ids of 242 fp32 (3% used) 46.5
+    // against 52.4 us; below either line cached loads are as fast in calls of
+    // up to 8192 bags (53 shapes of which less than 2% is used: 1.00) and
+    // faster the more is used (33 with a tenth and more: 1.12 times the speed;
+    // 2 x 322 bags of 49 ids of 512 B in 20 K rows: 7.9 against 7.0, the team
+    // kernel 7.0), and in larger ones rows of no whole 16-byte chunks, whose
+    // pieces cross cache lines, ask for a line twice (9 tables of 720 K rows x
+    // 10272 bags of 47 ids of 227 fp32, 0.67 uses a row: 752 against 658, the
     // plain kernel 664; 38 tables of 11 K rows x 7880 bags of 14 ids of 217
-    // fp32 (10 uses) 690, 392 and 403.
-    route.stream = hint && rb >= 128 &&
-                   (cb == 16 || (buf.all_local * rb >= kStreamTableBytes && gathered <= buf.all_local / 10));
+    // fp32, 10 uses: 690, 392 and 403).
+    route.stream = hint && rb >= 128 && buf.all_local * rb >= kStreamTableBytes && gathered <= buf.all_local / 10;
     route.split = split_waves(bags, nnz, rb, dtype);
     route.bags_per_block = route.split > 1 ? 1 : kWavesPerBlock;
     // Each XCD a run of workgroups under the hint, as with teams (64 ids of
-    // 32 bf16 in 100 K rows: 58 against 42), but not in small batches,
-    // where finding the run costs 0.3 us, nor where eight tables at a time
-    // would push each other's reused rows out of the caches: cached loads
-    // from tables of over 32 MB, a row in four or more used (0.67 uses a
-    // row, above: 776 against 658; tables of 11 K rows, above: 346 against
-    // 392; 4 tables x 34679 bags of 15 ids of 228 fp16, a row in
+    // 32 bf16 in 100 K rows: 58 against 42), but not in small batches, where
+    // finding the run costs 0.3 us, nor where eight tables at a time would
+    // push each other's reused rows out of the caches: rows of no whole
+    // 16-byte chunks from tables of over 32 MB, a row in four or more used
+    // (0.67 uses a row, above: 776 against 658; tables of 11 K rows, above:
+    // 346 against 392; 4 tables x 34679 bags of 15 ids of 228 fp16, a row in
     // twelve used: 153 against 165).
-    route.xcd_runs = hint && bags > kFewBagsMax &&
-                     (cb == 16 || buf.local_rows * rb <= kXcdTableBytes || gathered <= buf.all_local / 4);
+    // And for over 128 bags of one id, hinted or not, where an XCD would
+    // otherwise read a line of ids and offsets for four bags' sake (new ids, 27
+    // shapes: 0.89 of the time, the same ids again, 23: 1.03; 348 bags of 36
+    // bf16 4.7 against 4.3 us, the team kernel 4.1).
+    route.xcd_runs = (nnz < bags + bags / 2 && bags > 128) ||
+                     (hint && bags > kFewBagsMax &&
+                      (cb == 16 || buf.local_rows * rb <= kXcdTableBytes || gathered <= buf.all_local / 4));
     return route;
 }
 

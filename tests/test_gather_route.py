@@ -66,3 +66,24 @@ def test_large_batches_take_the_wave_kernel_where_a_team_is_a_wave_too():
     assert route(64, eb.EB_F16, 2, 4000, 16, 1_000_000, local=250_000).kernel == WAVE
     assert route(64, eb.EB_F16, 2, 4000, 15, 1_000_000).kernel == TEAM
     assert route(64, eb.EB_F16, 2, 55087, 100, 0).kernel == TEAM  # no rows at all
+
+
+def test_small_batches_are_cached_unless_no_row_comes_back():
+    for D, dtype in ((128, eb.EB_F32), (64, eb.EB_F16), (189, eb.EB_F16)):
+        for bags in (300, 2000):
+            for rows, nt in ((20_000, 0), (5_000_000, 1)):
+                r = route(D, dtype, 4, bags, 49, rows, hint=True)
+                assert (r.kernel, r.non_temporal) == (WAVE, nt), (D, bags, rows)
+                assert route(D, dtype, 4, bags, 49, rows).non_temporal == 0
+    assert route(128, eb.EB_F32, 4, 300, 49, 20_000, hint=True, align=2).kernel == PLAIN  # fp32 rows off 4 bytes
+
+
+def test_bags_of_one_id_run_in_order_on_each_xcd():
+    for D, dtype in ((36, eb.EB_BF16), (128, eb.EB_F32), (267, eb.EB_F16)):
+        assert not route(D, dtype, 1, 128, 1, 1_000_000).xcd_runs
+        for bags in (129, 2000, 50000):
+            for hint in (False, True):
+                r = route(D, dtype, 1, bags, 1, 1_000_000, hint=hint)
+                assert r.kernel == TEAM or r.xcd_runs
+                r = route(D, dtype, 1, bags, 2, 1_000_000)
+                assert not r.xcd_runs
