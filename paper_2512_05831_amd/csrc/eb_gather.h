@@ -892,13 +892,18 @@ inline bool use_wave(int64_t rb, int cb, const Shape &whole, int team_lanes, boo
     return gathered >= (double)(ids < kWave ? ids : kWave) * (double)bags;
 }
 
-// Waves per bag of the wave kernel, a power of two: more than one when a bag
-// per wave would leave at least half the GPU's wave slots empty, as long as a
-// wave keeps 48 ids and the partial sums fit 32 KB of LDS (64-column fp32
-// rows, 1 / 2 / 4 / 8 / 16 waves: 32 bags of 100 ids 5.0 / 4.7 / 4.4 / 4.5 /
-// 4.6 us, of 2000 ids 59.0 / 31.4 / 18.2 / 11.2 / 10.3; 512 bags of 400 ids
-// 15.6 / 11.1 / 10.5 / 10.4 / 10.3; 2048 bags of 400 ids 27.7 / 29.2 / 28.3 /
-// 28.2 / 30.5; the team kernel: 5.6, 49.4, 14.2, 28.4).
+// Waves per bag of the wave kernel, a power of two: more than one in calls of
+// up to 2048 bags of 48 ids and more on average, doubled while the wave slots
+// that are then taken stay within a half and a wave keeps 24 ids on average
+// (its windows of 64 are given out whole, so even lengths leave some waves none;
+// ragged ones gain from the next one: 52 bags of 28 to 84 ids 6.7 against 5.7
+// us), and the partial sums fit 32 KB of LDS.  64-column fp32 rows, 1 / 2 / 4 /
+// 8 / 16 waves: 32 bags of 100 ids 5.0 / 4.7 / 4.4 / 4.5 / 4.6 us, of 2000 ids
+// 59.0 / 31.4 / 18.2 / 11.2 / 10.3; 512 bags of 400 ids 15.6 / 11.1 / 10.5 /
+// 10.4 / 10.3; 2048 bags of 400 ids 27.7 / 29.2 / 28.3 / 28.2 / 30.5 (the team
+// kernel: 5.6, 49.4, 14.2, 28.4); the last is the shape found where two waves
+// lose, ragged bags there gain (2019 bags of 147 to 441 ids of 128 B 12.0
+// against 9.6).
 inline int split_waves(int64_t bags, int64_t nnz, int64_t rb, int dtype)
 {
     const int limit = split_limit((rb + 15) / 16, dtype);

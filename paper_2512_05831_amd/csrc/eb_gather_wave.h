@@ -196,7 +196,9 @@ __global__ __launch_bounds__(kWave *wave_block(C, DT)) void eb_gather_wave(const
 
     const int64_t L = e - s;
     float *dst = a.out + b * a.ldo + a.col[t];
-    if (split > 1) {
+    // The first wave has all of a bag of one window, and ends it alone.
+    if (split > 1 && L <= kWave && wave > 0) return;
+    if (split > 1 && L > kWave) {
         // Chunk by chunk, as loaded: the last one holds the row's last kEpc elements.
         const int width = a.chunks * kEpc;
         if (g == 0) {

@@ -68,6 +68,15 @@ def test_split_bags(D, dtype, bags, length, weighted, itype, device):
     check(D, dtype, lengths, 1, device, weighted=weighted, itype=itype)
 
 
+@pytest.mark.parametrize("D,dtype", [(64, wl.F32), (189, wl.F16), (300, wl.F32)])
+@pytest.mark.parametrize("weighted,itype", [(False, np.int64), (True, np.int32)])
+def test_split_bags_around_one_window(D, dtype, weighted, itype, device):
+    """Bags of up to one window of 64 ids among longer ones: in a split call the
+    first wave ends them alone."""
+    lengths = [64, 65, 0, 63, 200, 1, 64, 128, 129, 64, 40, 300]
+    check(D, dtype, lengths, 2, device, weighted=weighted, itype=itype)
+
+
 @pytest.mark.parametrize("D,dtype", [(32, wl.F32), (128, wl.F32), (256, wl.BF16), (512, wl.F16), (75, wl.F16)])
 def test_large_batch_of_windows(D, dtype, device):
     lengths = np.random.default_rng(D).integers(0, 130, 2 * 4200)
