@@ -208,10 +208,11 @@ int eb_forward(const eb_tables *tables, int32_t T, const int64_t *rows, int32_t 
  * pointer is aligned to, and whose results (4 floats per 16 bytes of fp32,
  * 8 of fp16 / bf16; at most 16 bytes) the output rows' alignment (out, ldo
  * and every out_cols[t]) allows to store as one access.  Rows of 16 bytes to
- * 8 KB that allow none of them (and, in small batches or long bags, all
- * ragged ones) are read in unaligned 16-byte pieces where every table holds
- * less than 4 GB of gatherable rows and is aligned to its element size.  Other
- * rows take a plain element-by-element path: correct, but slower.
+ * 8 KB that allow none of them, and in small batches or long bags those of up
+ * to 2 KB that do, are read in 16-byte pieces of any alignment by a wave per
+ * bag, where every table holds less than 4 GB of gatherable rows and is aligned
+ * to its element size.  Other rows that allow none take a plain
+ * element-by-element path: correct, but slower.
  *
  * Errors: those of eb_forward, and EB_ERR_INVALID for an unknown index_type,
  * weights with EB_MEAN, ldo < 1, a table's columns outside [0, ldo),

@@ -50,11 +50,7 @@ struct TwoArgs {
     int32_t groups_per_table;
 };
 
-template <typename T>
-__device__ __forceinline__ T scalar_load(const T *p)
-{
-    return *(const __attribute__((address_space(4))) T *)(uint64_t)p;
-}
+using eb_detail::scalar_load;
 
 // The chunk's lanes by owner.  kOwners: 8 (3-bit compare tree), 16 (by pairs
 // of blocks), 32 and 64 (binary search within the eighths).

@@ -1,5 +1,5 @@
 // Wave gather: a whole wave per bag, or up to 16 waves (one workgroup) for one
-// long bag.  Selection by shape in plan_gather (eb_gather.h), instantiated in
+// long bag.  Selection by shape in choose_route (eb_gather.h), instantiated in
 // eb_gather_wave.hip and eb_gather_wave_weighted.hip.
 //
 // What bounds the gather when rows come from the caches is vector issue and
@@ -24,8 +24,11 @@
 #pragma once
 
 #include "eb_gather.h"
+#include "eb_internal.h"
 
 namespace eb_gather {
+
+using eb_detail::scalar_load;
 
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 
@@ -44,14 +47,6 @@ __device__ __forceinline__ i32x4 table_rsrc(const char *p, uint32_t pitch, uint3
     r[2] = (int)n;
     r[3] = 0x00020000;
     return r;
-}
-
-// A wave-uniform load through the scalar cache (the offsets are not written
-// by this kernel).
-template <typename T>
-__device__ __forceinline__ T scalar_load(const T *p)
-{
-    return *(const __attribute__((address_space(4))) T *)(uint64_t)p;
 }
 
 template <int DT, bool kW>
@@ -95,10 +90,12 @@ __device__ __forceinline__ void wave_lds_sync()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Rows in flight per lane group: about 4 KB per wave, never more than a
-// window of 64, and registers for 8 waves per SIMD up to 1-KB rows (2 instead
-// of 4 for 128-B rows: 15% slower; 8 instead of 4 for 512-B rows: within 1%;
-// 4 instead of 8 for 768-B rows in bags of 64: 4% slower).
+// Rows in flight per lane group, U * C KB per wave: 4 for rows of 65 to 512
+// bytes, less for narrower ones (a pass stays within a window of 64), 5 to 8
+// for wider ones; registers for 8 waves per SIMD up to 512-B rows and for 5 and
+// more up to 2 KB (2 instead of 4 for 128-B rows: 15% slower; 8 instead of 4 for
+// 512-B rows: within 1%; 4 instead of 8 for 768-B rows in bags of 64: 4%
+// slower).
 constexpr int wave_unroll(int R, int C)
 {
     return C > 1 ? (C >= 5 ? 1 : C >= 3 ? 2 : 4) : R == 64 ? 8 : R >= 8 ? 4 : R >= 2 ? 2 : 1;
