@@ -1,9 +1,11 @@
-"""GPU parity for the team kernel's 8- and 4-byte chunks.
+"""GPU parity for rows of 8- and 4-byte chunks.
 
 Rows load in the widest chunk of 16, 8 or 4 bytes that divides the row,
 that every table pointer allows, and whose results the output rows' alignment
-lets the kernel store as one access; otherwise the plain kernel runs.  These
-cases reach each width through the row size (D = 100 fp16 is 200 bytes, D = 3
+lets the team kernel store as one access.  Small batches, long bags and rows
+that none divides go to the wave kernel, which reads any of them in unaligned
+16-byte pieces; test_gpu_large_tables.py keeps every shape on the team or plain
+kernel.  These cases reach each width through the row size (D = 100 fp16 is 200 bytes, D = 3
 fp32 12 bytes), through tables placed 4 or 8 bytes past a 16-byte boundary, and
 through outputs whose rows start 4 or 8 bytes off one, with shards,
 out-of-range ids, both cache policies, small and large batches, sum and mean,
@@ -42,7 +44,7 @@ def shifted(t, dtype, shift_bytes, device):
     return view
 
 
-# (D, dtype, table shift bytes, output shift floats): expected chunk bytes in the comment
+# (D, dtype, table shift bytes, output shift floats): the team kernel's chunk bytes in the comment
 CASES = [
     (100, wl.F16, 0, 0),   # 200-B rows: 8
     (36, wl.F16, 0, 0),    # 72 B: 8
@@ -53,7 +55,7 @@ CASES = [
     (32, wl.F32, 0, 2),    # 128 B, output rows 8 B off: 8
     (60, wl.F32, 0, 1),    # 240 B, output rows 4 B off: 4
     (50, wl.BF16, 0, 0),   # 100 B: 4
-    (130, wl.BF16, 0, 0),  # 260 B: 4 exceeds one chunk per lane at 64 lanes x 4 B: plain
+    (130, wl.BF16, 0, 0),  # 260 B: 4 exceeds one chunk per lane at 64 lanes x 4 B: none
 ]
 
 

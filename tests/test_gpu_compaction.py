@@ -1,12 +1,13 @@
 """Shard filtering when few of a bag's ids are local.
 
-The team kernel writes the ids gathered on this GPU to the front of each LDS
-window of ids (in position order) and pools only those.  These cases mix bags
+The team and wave kernels write the ids gathered on this GPU to the front of each
+LDS window of ids (in position order) and pool only those.  These cases mix bags
 whose ids are all local, none local and about 1 in 10 local, with lengths
-from 0 to 700 (so windows of every team width hold all, some or none of a
-bag's local ids, and bags span several windows), over every team shape, both
-cache policies, small and large batches (which change the mapping), int32
-ids and per-sample weights.  Tables hold dyadic values, so every sum is
+from 0 to 700 (so windows hold all, some or none of a bag's local ids, and bags
+span several windows), over every row shape, both cache policies, small and large
+batches (which change the mapping), int32 ids and per-sample weights.  The small
+batches' rows of 16 bytes to 2 KB run the wave kernel; test_gpu_large_tables.py
+takes the team kernel's windows through the same.  Tables hold dyadic values, so every sum is
 exact in any order and must equal the oracle bit for bit; hit counts too.
 """
 import numpy as np

@@ -1,5 +1,5 @@
-"""GPU parity of the kernels that tables of 4 GB and more take, and of the wave
-kernel at its address limit.
+"""GPU parity of the kernels that tables of 4 GB and more take, of the wave
+kernel's streamed rows (tables of 2 GB and more), and of it at its address limit.
 
 The wave kernel's row offsets are 32-bit products, so a call with a larger table
 takes the team kernel (16-, 8- and 4-byte chunks; small-batch, normal and narrow
@@ -55,40 +55,31 @@ SHAPES = [
 ]
 
 
-@pytest.mark.parametrize("D,dtype,tshift,oshift,chunk", SHAPES)
-@pytest.mark.parametrize("B,max_len", [(7, 700), (3000, 30), (20000, 10)])
-@pytest.mark.parametrize("hint", [0, eb.EB_HINT_STREAM_ROWS])
-def test_kernels_of_large_tables(D, dtype, tshift, oshift, chunk, B, max_len, hint, memory, device):
+def check(D, dtype, tshift, oshift, B, max_len, hint, big, memory, device):
+    """Two tables, the first of `big` rows.  Returns the route of the calls."""
     T = 2
-    rb = D * ES[dtype]
-    if rb > 2048:
-        B = min(B, 1000)
-    big = (1 << 32) // rb + 1
     g = np.random.default_rng(D + 7 * B + tshift + 100 * oshift)
     off = wl.offsets_from_lengths(g.integers(0, max_len + 1, T * B))
     idx = g.integers(LO - 200, HI, int(off[-1]), dtype=np.int64)
     idx[5::17] = 2**31 - 1 - g.integers(0, 9, idx[5::17].size)  # past the last row of both tables
     assert LO + big < 2**31 - 9
-    r = route(D, dtype, T, B, idx.size / (T * B), LO + big, big, hint=bool(hint), align=tshift or 16, out_align=4 * oshift or 16)
-    assert (r.kernel, r.chunk_bytes) == (TEAM if chunk else PLAIN, chunk)
-    if B == 7 or rb <= 2048:
-        assert r.small_batch == (1 if chunk and B == 7 else 0)
     tables = [wl.table(D, t, D, dtype, LO, HI, values="dyadic") for t in range(T)]
     et = eb.EmbeddingBagTables([place(memory, tables[0], dtype, device, big, tshift),
                                 place(None, tables[1], dtype, device, HI - LO, tshift)],
                                rows=[LO + big, HI], shard_lo=LO)
-    W = T * D + 4 - T * D % 4
+    W = T * (D + 3) // 4 * 4 + 4
+    cols = [0, (D + 3) // 4 * 4]
     w = (g.integers(-8, 9, idx.size) / 4.0).astype(np.float32)  # dyadic weights: exact products
     for mode, weights, itype in ((wl.SUM, None, torch.int64), (wl.MEAN, None, torch.int32), (wl.SUM, w, torch.int32)):
         buf = torch.full((B * W + 4,), float("nan"), dtype=torch.float32, device=device)
         out = buf[oshift:oshift + B * W].view(B, W)
         hits = torch.full((B, T), -7, dtype=torch.int32, device=device)
         et.forward_ex(torch.from_numpy(idx).to(device).to(itype), torch.from_numpy(off).to(device).to(itype), B,
-                      mode=mode | hint, out=out, out_cols=[0, W - D if chunk else D], hits=hits,
+                      mode=mode | hint, out=out, out_cols=cols, hits=hits,
                       weights=None if weights is None else torch.from_numpy(weights).to(device))
         torch.cuda.synchronize()
-        got = out.cpu().numpy()
-        got = np.concatenate([got[:, :D], got[:, W - D:] if chunk else got[:, D:2 * D]], axis=1).astype(np.float64)
+        got = out.cpu().numpy().astype(np.float64)
+        got = np.concatenate([got[:, c:c + D] for c in cols], axis=1)
         ref, ref_hits, _ = oracle.forward(tables, [HI] * T, D, dtype, idx, off, B, mode, LO, HI, weights=weights)
         assert np.array_equal(hits.cpu().numpy(), ref_hits)
         if mode == wl.SUM:
@@ -96,6 +87,31 @@ def test_kernels_of_large_tables(D, dtype, tshift, oshift, chunk, B, max_len, hi
         else:  # one division after an exact sum
             assert np.all(np.abs(got - ref) <= np.abs(ref) * 2.0 ** -24)
     et.close()
+    return route(D, dtype, T, B, idx.size / (T * B), LO + big, big, hint=bool(hint), align=tshift or 16,
+                 out_align=4 * oshift or 16)
+
+
+@pytest.mark.parametrize("D,dtype,tshift,oshift,chunk", SHAPES)
+@pytest.mark.parametrize("B,max_len", [(7, 700), (3000, 30), (20000, 10)])
+@pytest.mark.parametrize("hint", [0, eb.EB_HINT_STREAM_ROWS])
+def test_kernels_of_large_tables(D, dtype, tshift, oshift, chunk, B, max_len, hint, memory, device):
+    rb = D * ES[dtype]
+    if rb > 2048:
+        B = min(B, 1000)
+    r = check(D, dtype, tshift, oshift, B, max_len, hint, (1 << 32) // rb + 1, memory, device)
+    assert (r.kernel, r.chunk_bytes) == (TEAM if chunk else PLAIN, chunk)
+    if B == 7 or rb <= 2048:
+        assert r.small_batch == (1 if chunk and B == 7 else 0)
+
+
+@pytest.mark.parametrize("D,dtype", [(64, wl.F16), (35, wl.F32), (128, wl.BF16), (189, wl.F16), (128, wl.F32), (256, wl.F32),
+                                     (512, wl.F32), (257, wl.F32), (701, wl.F32), (1025, wl.BF16), (1290, wl.F32),
+                                     (3100, wl.F16), (3700, wl.BF16), (4095, wl.F16)])
+@pytest.mark.parametrize("B,max_len", [(7, 700), (1000, 40)])
+def test_streamed_rows(D, dtype, B, max_len, memory, device):
+    r = check(D, dtype, 0, 0, B, max_len, eb.EB_HINT_STREAM_ROWS, (3 << 30) // (D * ES[dtype]), memory, device)
+    assert (r.kernel, r.non_temporal) == (WAVE, 1)
+    assert (r.split > 1) == (B == 7)
 
 
 @pytest.mark.parametrize("D,dtype", [(189, wl.F16), (128, wl.F32), (8, wl.F16)])

@@ -124,7 +124,8 @@ def test_narrow_teams(D, dtype, hint, B):
     a wave keeps in flight per bag, take teams narrower than a wave: 256-B
     and 1-KB rows 16 lanes of 1 or 4 chunks (four bags per wave), 512-B rows
     32 lanes streamed and 16 lanes of 2 chunks cached, 400-B rows 32 lanes.
-    4 x 4500 bags switch them on; 4 x 1000 stay on the normal mapping.
+    4 x 4500 bags switch them on; 4 x 1000 go to the wave kernel (the team
+    kernel's normal mapping: test_gpu_large_tables.py).
     Out-of-range ids, a shard, sum and mean; dyadic tables exactly."""
     maxL = 30 if hint else 10
     for values in ("normal", "dyadic"):
@@ -281,6 +282,8 @@ def test_uses_only_the_first_T_tables_of_a_handle(device):
 
 @pytest.mark.parametrize("dtype", DT)
 def test_unaligned_table_takes_plain_path(dtype, device):
+    """Tables off every chunk's alignment: the plain path where a table holds 4 GB
+    (test_gpu_large_tables.py), here the wave kernel's unaligned pieces."""
     D, rows, B = 128, 1000, 40
     tables, r, idx, off = case(T=1, D=D, dtype=dtype, rows=rows, B=B, seed=11)
     w = to_device_table(tables[0], dtype, device)
