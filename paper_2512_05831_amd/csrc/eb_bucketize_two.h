@@ -7,8 +7,9 @@
 // every wave's ids per destination; in the second every workgroup adds up the
 // totals of the workgroups before it, and its waves read their ids again (now
 // in the L2s), place them, and write their bags' offsets from the same lane
-// masks: 10.3 and 22.5 us (kernels 3.7 + 6.2 and 7.1 + 16.7; the second is
-// bound by vector issue, about 60 instructions per 64 ids, and its start-up):
+// masks: 10.0 and 23.3 us (the kernels 3.6 + 6.2 and 6.8 + 16.9 under the
+// profiler, which adds to each; the second is bound by vector issue, about 60
+// instructions per 64 ids, and its start-up):
 //   * a workgroup takes consecutive bags of one table and its waves even runs
 //     of their ids, so that no wave waits for a long bag of another.  The
 //     range comes by two scalar loads, so the ids are on their way before the
