@@ -970,8 +970,8 @@ inline GatherRoute choose_route(int32_t D, int32_t dtype, const GatherBuffers &b
     // against 52.4 us; below either line cached loads are as fast in calls of
     // up to 8192 bags (53 shapes of which less than 2% is used: 1.00) and
     // faster the more is used (33 with a tenth and more: 1.12 times the speed;
-    // 2 x 322 bags of 49 ids of 512 B in 20 K rows: 7.9 against 7.0, the team
-    // kernel 7.0), and in larger ones rows of no whole 16-byte chunks, whose
+    // 2 x 322 bags of 49 ids of 512 B in 22 K rows: 8.0 against 6.0, the team
+    // kernel 7.6), and in larger ones rows of no whole 16-byte chunks, whose
     // pieces cross cache lines, ask for a line twice (9 tables of 720 K rows x
     // 10272 bags of 47 ids of 227 fp32, 0.67 uses a row: 752 against 658, the
     // plain kernel 664; 38 tables of 11 K rows x 7880 bags of 14 ids of 217
@@ -990,7 +990,7 @@ inline GatherRoute choose_route(int32_t D, int32_t dtype, const GatherBuffers &b
     // And for over 128 bags of one id, hinted or not, where an XCD would
     // otherwise read a line of ids and offsets for four bags' sake (new ids, 27
     // shapes: 0.89 of the time, the same ids again, 23: 1.03; 348 bags of 36
-    // bf16 4.7 against 4.3 us, the team kernel 4.1).
+    // bf16 in 50 K rows 3.6 against 3.5 us, the team kernel 3.6).
     route.xcd_runs = (nnz < bags + bags / 2 && bags > 128) ||
                      (hint && bags > kFewBagsMax &&
                       (cb == 16 || buf.local_rows * rb <= kXcdTableBytes || gathered <= buf.all_local / 4));
