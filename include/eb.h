@@ -67,15 +67,18 @@ enum { EB_SUM = 0, EB_MEAN = 1 };
 
 /* Reuse hint, OR-ed into eb_forward's `mode`.  EB_HINT_STREAM_ROWS tells the
  * library that the ids have little reuse (for example drawn uniformly from
- * tables much larger than the 256 MB last-level cache).  It then reads rows of
- * 128 bytes or more with non-temporal loads, which bypass L2 and the
- * last-level cache, gives each XCD a contiguous run of bags, and in large
- * batches pools rows of 128 bytes to 1 KB with one lane group per bag.  Faster for such ids, slower for skewed ones (hot rows then
- * miss the caches).  Without the hint, large batches of short bags (a mean
- * length below the rows the library keeps in flight per bag, as in the bags
- * one row block receives in a row-wise exchange) are pooled the same way.  It changes no hit count; by splitting a bag's rows
- * differently over lanes it may change the order of the fp32 additions and so
- * the last bits of a sum (every result stays within the same accuracy bound,
+ * tables much larger than the 256 MB last-level cache).  Large batches then read
+ * rows of 128 bytes or more in 16-byte chunks with non-temporal loads, which
+ * bypass L2 and the last-level cache, and pool those of up to 1 KB with one lane
+ * group per bag; other calls read such rows so where the tables hold 2 GB and
+ * more and the batch uses a row in ten or fewer.  Each XCD takes a contiguous
+ * run of bags, except in small batches and where ragged rows of large tables are
+ * reused.  Faster for such ids, slower for skewed ones (hot rows then miss the
+ * caches).  Without the hint, large batches of short bags (a mean length below
+ * the rows the library keeps in flight per bag, as in the bags one row block
+ * receives in a row-wise exchange) are pooled the same way.  It changes no hit
+ * count; by splitting a bag's rows differently over lanes it may change the
+ * order of the fp32 additions and so the last bits of a sum (every result stays within the same accuracy bound,
  * exact sums stay exact).  Repeated calls with the same mode give identical
  * bits. */
 enum { EB_HINT_STREAM_ROWS = 0x100 };
